@@ -665,13 +665,16 @@ static bool ks_rest_ok(const Layout& L, int64_t rest) {
     return gemm_ks_supported(L) && L.K <= kKsRestMaxK && rest <= kKsRestMaxTiles;
 }
 
-int launch_gemm256(const Layout& L, const uint16_t* A, const uint8_t* pk, uint16_t* C, int64_t M,
-                   void* ws, size_t ws_bytes, hipStream_t s, bool bf) {
+namespace {
+struct Gemm256Plan {
+    StreamK sk;          // sk.part not set yet
+    KsRange rest;
+};
+Gemm256Plan plan_gemm256(const Layout& L, int64_t M, int64_t ws_bytes, int cus) {
     const int tiles_m = (int)((M + kBM - 1) / kBM);
     const int tiles_n = (int)((L.N + kBN - 1) / kBN);
     const int tiles = tiles_m * tiles_n, chunks = (int)(L.K / (kBK * kCS));
     const int64_t need = gemm256_workspace_bytes(L, M);
-    const int cus = device_cus(s);
     StreamK sk{0, 0, nullptr, 0};
     // Otherwise (with a workspace) stream-K; splitting every tile keeps at
     // least kSkMinUnits K chunks per block.  With at least one full wave of
@@ -698,7 +701,7 @@ int launch_gemm256(const Layout& L, const uint16_t* A, const uint8_t* pk, uint16
         sk = StreamK{Gr, 0, nullptr, dp_rounds};
         rest.tile0 = dp_rounds * Gr;
         rest.count = tiles - rest.tile0;
-    } else if (ws && need > 0 && (int64_t)ws_bytes >= need && !dp_ok) {
+    } else if (need > 0 && ws_bytes >= need && !dp_ok) {
         int G = std::min(cus, kSkMaxGroups);
         if (G > kXcds) G -= G % kXcds;
         int dp_rounds = tiles / G;
@@ -712,9 +715,38 @@ int launch_gemm256(const Layout& L, const uint16_t* A, const uint8_t* pk, uint16
         const int64_t units = (int64_t)(tiles - dp_rounds * G) * chunks;
         if (dp_rounds == 0) G = (int)std::min<int64_t>(G, std::max<int64_t>(1, units / kSkMinUnits));
         if (G > kXcds) G -= G % kXcds;
-        sk = StreamK{G, (int)units, reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + kWsCounterBytes),
-                     dp_rounds};
+        sk = StreamK{G, (int)units, nullptr, dp_rounds};
     }
+    return {sk, rest};
+}
+}  // namespace
+
+// Measured: a whole tile 8 us and 20 ns per row of K (K = 4096: 90 us a
+// round); stream-K 26 us (refills, parked partials, the reduction launch) and
+// 21 ns per row of K that a block computes (K = 14336, N = 4096, M = 256, 1024,
+// 2048: 48, 108, 182 us).
+int64_t gemm256_cost(const Layout& L, int64_t M, int64_t ws_bytes, int64_t cus, bool bf) {
+    const Gemm256Plan p = plan_gemm256(L, M, ws_bytes, (int)cus);
+    const int64_t tiles = ((M + kBM - 1) / kBM) * ((L.N + kBN - 1) / kBN);
+    if (p.sk.groups == 0) return (tiles + cus - 1) / cus * (8000 + 20 * L.K);
+    if (p.rest.count > 0)
+        return p.sk.dp_rounds * (8000 + 20 * L.K) +
+               (8 * p.rest.count + cus - 1) / cus * gemm_ks_round_cost(L, false, bf);
+    const int64_t chunks = L.K / (kBK * kCS);
+    return 26000 + 21 * kBK * kCS * (p.sk.dp_rounds * chunks + p.sk.units / p.sk.groups);
+}
+
+int launch_gemm256(const Layout& L, const uint16_t* A, const uint8_t* pk, uint16_t* C, int64_t M,
+                   void* ws, size_t ws_bytes, hipStream_t s, bool bf) {
+    const int tiles_m = (int)((M + kBM - 1) / kBM);
+    const int tiles_n = (int)((L.N + kBN - 1) / kBN);
+    const int tiles = tiles_m * tiles_n, chunks = (int)(L.K / (kBK * kCS));
+    const int cus = device_cus(s);
+    Gemm256Plan plan = plan_gemm256(L, M, ws ? (int64_t)ws_bytes : 0, cus);
+    StreamK& sk = plan.sk;
+    const KsRange& rest = plan.rest;
+    if (sk.groups && rest.count == 0)
+        sk.part = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + kWsCounterBytes);
     if (log_enabled())
         log_plan("gemm256_kernel<%d,%d,%s> M=%lld K=%lld N=%lld G=%d: %dx%d tiles of 256x256, %d K chunks, "
                  "%s, %d CUs, order %s",
@@ -741,11 +773,6 @@ int launch_gemm256(const Layout& L, const uint16_t* A, const uint8_t* pk, uint16
                       tiles_n, cm, sk.groups, sk.units, chunks, tile0, total);
     return launch(stream_k_reduce_kernel<false>, grid, dim3(256), 0, s, part, C, (int)M, (int)L.N, tiles_m,
                   tiles_n, cm, sk.groups, sk.units, chunks, tile0, total);
-}
-
-bool gemm256_fills_device(const Layout& L, int64_t M, hipStream_t s) {
-    const int64_t tiles = ((M + kBM - 1) / kBM) * ((L.N + kBN - 1) / kBN);
-    return 4 * tiles >= 3 * (int64_t)device_cus(s);
 }
 
 }  // namespace tf

@@ -529,9 +529,8 @@ int launch_ks_bits(const Layout& L, const uint16_t* A, const uint8_t* pk, uint16
 // 100 against 32.4, 67, 103.5 us) and K = 8192, N = 8192, M = 200 (39.2
 // against 56 us).
 constexpr int64_t kKsWideCostHalves = 3;    // a 64 x 256 tile's time in halves of a 64 x 128 tile's
-bool gemm_ks_wide(const Layout& L, int64_t M, hipStream_t s) {
+bool gemm_ks_wide(const Layout& L, int64_t M, int64_t cus) {
     if (L.bits != 4) return false;
-    const int64_t cus = device_cus(s);
     const int64_t tm = (M + 63) / 64;
     const int64_t t128 = tm * ((L.N + 127) / 128), t256 = tm * ((L.N + 255) / 256);
     return 2 * t128 > kKsWideCostHalves * ((t256 + cus - 1) / cus) * cus;
@@ -557,9 +556,22 @@ bool gemm_ks_supported(const Layout& L) {
     return L.K % chunk_rows == 0 && L.K / chunk_rows >= kKsWaves && (L.group & (L.group - 1)) == 0;
 }
 
+// Measured rounds (see the choice of kernel in tf_gemm.hip): 64 x 128 tiles at
+// K = 2048, 4096, 14336 11.5, 19, 49 us in fp16, 13.7, 22.5, 62 in bf16;
+// 64 x 256 at K = 4096 34.4 and 40.4 us.
+int64_t gemm_ks_round_cost(const Layout& L, bool wide, bool bf) {
+    if (wide) return bf ? 11000 + 7200 * L.K / 1000 : 9500 + 6100 * L.K / 1000;
+    return 6000 + (bf ? 4000 : 3100) * L.K / 1000;
+}
+int64_t gemm_ks_cost(const Layout& L, int64_t M, int64_t cus, bool bf) {
+    const bool wide = gemm_ks_wide(L, M, cus);
+    const int64_t bn = wide ? 256 : 128, tiles = ((M + kKsBM - 1) / kKsBM) * ((L.N + bn - 1) / bn);
+    return (tiles + cus - 1) / cus * gemm_ks_round_cost(L, wide, bf);
+}
+
 int launch_gemm_ks(const Layout& L, const uint16_t* A, const void* packed, uint16_t* C, int64_t M,
                    hipStream_t s, bool bf) {
-    return launch_any(L, A, packed, C, M, KsRange{0, 0, 0, 0, 0}, s, bf, gemm_ks_wide(L, M, s));
+    return launch_any(L, A, packed, C, M, KsRange{0, 0, 0, 0, 0}, s, bf, gemm_ks_wide(L, M, device_cus(s)));
 }
 
 int launch_gemm_ks_range(const Layout& L, const uint16_t* A, const void* packed, uint16_t* C, int64_t M,

@@ -2,16 +2,14 @@
 // matrix-vector products; Section 4.3 "GEMV microkernel"; Section 4.4).
 //
 // y[m, n] = sum_k x[m, k] * s[g, n] * (q[k, n] - z[g, n]),  1 <= M <= 8, on
-// the vector ALU only.  The same streaming kernel with 16, 32 or 64 row
-// slots serves the GEMM entry points for few rows (skinny prefill,
-// 4 <= M <= 64) on the matrix cores (v_mfma_f32_16x16x32_f16 / _bf16), where
-// the weights, not the matrix cores, bound the time.  With 16 or 32 slots the
-// codes themselves (exact 16-bit integers o + q) are the B operand: per group
-// the matrix core forms sum A * (o + q) and, against an operand of ones, the
-// row sums of A, and the group closes with s * (acc - (o + z) * rowsum), which
-// leaves the vector ALU a few instructions per dword instead of the whole
-// dequantization.  With 64 slots (too many group sums for the registers) each
-// weight is dequantized with the GEMM's code and fed to the matrix core.
+// the vector ALU only.  The same streaming kernel with 16 or 32 row slots
+// serves the GEMM entry points for few rows (skinny prefill, 4 <= M <= 32) on
+// the matrix cores (v_mfma_f32_16x16x32_f16 / _bf16), where the weights, not
+// the matrix cores, bound the time.  There the codes themselves (exact 16-bit
+// integers o + q) are the B operand: per group the matrix core forms
+// sum A * (o + q) and, against an operand of ones, the row sums of A, and the
+// group closes with s * (acc - (o + z) * rowsum), which leaves the vector ALU
+// a few instructions per dword instead of the whole dequantization.
 //
 // Mapping (the GPU form of the principle of Section 4.4: every compute unit
 // streams its own weight slice, the activations are shared, each workgroup
@@ -60,15 +58,11 @@ struct GemvCfg {
     static constexpr int T = BITS == 4 ? 4 : 2;      // columns per lane
     static constexpr int PW = BITS == 4 ? 64 : 32;   // panel width
     static constexpr bool FACT = M <= kFactMaxM;
-    // 16, 32 or 64 row slots (GEMM calls with few rows): matrix cores, A
-    // read per atom, MB blocks of 16 rows
+    // 16 or 32 row slots (GEMM calls with few rows): matrix cores, A read per
+    // atom, MB blocks of 16 rows; the codes themselves are the B operand and
+    // the scale and zero-point are applied per group
     static constexpr bool MF = M > TF_GEMV_MAX_M;
     static constexpr int MB = MF ? M / 16 : 1;
-    // matrix-core factored form (16 or 32 row slots): the codes themselves
-    // are the B operand and the scale and zero-point are applied per group
-    // (64 slots keep the dequantized operand: the group sums would not fit
-    // in registers)
-    static constexpr bool MFF = MF && M <= 32;
     static constexpr int XR = MF ? 1 : M;             // rows of x staged in LDS
     static constexpr int CR = FACT ? M : 1;           // rows of slice sums
 };
@@ -100,9 +94,9 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
     // (in bounds) and are never stored.
     using Cfg = GemvCfg<BITS, M>;
     constexpr int U = kGemvU, T = Cfg::T, PW = Cfg::PW;
-    constexpr bool FACT = Cfg::FACT, MF = Cfg::MF, MFF = Cfg::MFF;
+    constexpr bool FACT = Cfg::FACT, MF = Cfg::MF;
     constexpr int NT = WAVES * 64;
-    static_assert(!MF || M == 16 || M == 32 || M == 64, "the matrix-core form holds 16, 32 or 64 rows");
+    static_assert(!MF || M == 16 || M == 32, "the matrix-core form holds 16 or 32 rows");
     constexpr int MB = Cfg::MB;
     static_assert(SEG == 0 || U % SEG == 0, "segments tile a round");
     static_assert(U % D == 0, "the load ring tiles a round");
@@ -117,7 +111,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
     // (84 KB together at most, W4 with 3 rows; one workgroup per compute unit
     // either way), so a wave that has finished writes its sums while others
     // still read their staging, with no barrier in between; the matrix-core
-    // form's reduction buffer (up to 64 rows) reuses the staging storage.
+    // form's reduction buffer (up to 32 rows) reuses the staging storage.
     struct SmemApart {
         Stage st[WAVES];
         float red[WAVES][M][PW];
@@ -271,11 +265,11 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
         float acc[M][TE];                // factored form: sums of x * code of the open segment
         float bo[M], sx[M];              // ... and the segment's sums of x * offset and of x
         DqConst<BF> kq[TE];              // dequant form: the open segment's scale and zero-point
-        // matrix-core factored form: the open segment's sums of A x code and
+        // matrix-core form: the open segment's sums of A x code and
         // of A (row sums, the same in every column of a block)
-        float4_t accg[MFF ? MB : 1][MFF ? T : 1], rsum[MFF ? MB : 1];
+        float4_t accg[MF ? MB : 1][MF ? T : 1], rsum[MF ? MB : 1];
         auto open = [&]() {
-            if constexpr (MFF) {
+            if constexpr (MF) {
 #pragma unroll
                 for (int b = 0; b < MB; ++b) {
                     rsum[b] = float4_t{0.f, 0.f, 0.f, 0.f};
@@ -298,10 +292,10 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
             }
         };
         // close the open segment: y += s * (acc - bo - z * sx); matrix-core
-        // factored form: y += s * (acc - (o + z) * (row sum of A)), o the
+        // form: y += s * (acc - (o + z) * (row sum of A)), o the
         // codes' offset
         auto close = [&]() {
-            if constexpr (MFF) {
+            if constexpr (MF) {
                 const uint16_t* sp = reinterpret_cast<const uint16_t*>(sbytes + (gl * PW + c * T) * 2);
                 const uint8_t* zp = zbytes + gl * PW + c * T;
                 constexpr float off = BF ? (BITS == 4 ? 128.f : 0.f) : 1024.f;
@@ -329,7 +323,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
             }
         };
 
-        if constexpr (FACT || MFF || SEG > 0) open();
+        if constexpr (FACT || MF || SEG > 0) open();
 #pragma unroll
         for (int i = 0; i < U; ++i) {
             const int j = r * U + i;      // atom of the run
@@ -345,7 +339,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
                     aring[b][i % D] = load_afrag(b, j + D);
                 }
             }
-            if constexpr (MFF) {
+            if constexpr (MF) {
                 // row sums of this atom's A, by the matrix core against ones
                 const uint32_t one2 = BF ? 0x3F803F80u : 0x3C003C00u;
                 const u32x4 ones = {one2, one2, one2, one2};
@@ -353,7 +347,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
                 for (int b = 0; b < MB; ++b) rsum[b] = mfma16<BF>(afrag[b], ones, rsum[b]);
             }
             // dequant form, group size known at run time: this atom's metadata
-            if constexpr (!FACT && !MFF && SEG == 0) open();
+            if constexpr (!FACT && !MF && SEG == 0) open();
             u32x4 xv[Cfg::XR];
             if constexpr (!MF) {
 #pragma unroll
@@ -380,7 +374,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
 #pragma unroll
             for (int t = 0; t < TE; ++t) {
                 uint32_t P[4];
-                if constexpr (MFF) {
+                if constexpr (MF) {
                     // the codes as exact 16-bit integers o + q: fp16 1024 + q,
                     // bf16 128 + q (4-bit) or q (8-bit, converted)
                     if constexpr (BITS == 4) {
@@ -422,12 +416,6 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
                 } else {
                     const u32x4 wu = dq_operand<BF, BITS>(wd[BITS == 4 ? t : 2 * t], wd[BITS == 4 ? t : 2 * t + 1],
                                                           magic, kq[t]);
-                    if constexpr (MF) {
-                        // the dequantized dword is the B operand of columns c + 16 t
-#pragma unroll
-                        for (int b = 0; b < MB; ++b) macc[b][t] = mfma16<BF>(afrag[b], wu, macc[b][t]);
-                        continue;
-                    }
 #pragma unroll
                     for (int q = 0; q < 4; ++q) P[q] = wu[q];
                 }
@@ -455,7 +443,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
                         ++gl;
                         pos = 0;
                     }
-                    if constexpr (FACT || MFF || SEG > 0) open();
+                    if constexpr (FACT || MF || SEG > 0) open();
                 }
             }
         }
@@ -727,7 +715,8 @@ int64_t gemv_workspace_bytes(const Layout& L, int64_t M) {
     return M >= 1 && M <= TF_GEMV_MAX_M ? workspace_for_slots(L, M) : 0;
 }
 
-// row slots of the matrix-core form for M rows: 16, 32 or 64
+// row slots of the matrix-core form for M rows: 16 or 32 (64: only the
+// promised workspace of 33..64 rows, see tf_internal.h)
 static int64_t skinny_slots(int64_t M) { return M <= 16 ? 16 : M <= 32 ? 32 : 64; }
 
 int64_t skinny_workspace_bytes(const Layout& L, int64_t M) {
@@ -749,15 +738,14 @@ int launch_skinny_bits(const Layout& L, const uint16_t* A, const uint8_t* pk, ui
                        int64_t M, void* ws, hipStream_t s) {
     switch (skinny_slots(M)) {
         case 16: return launch_m<BITS, 16, BF>(L, A, pk, C, ws, s, (int)M);
-        case 32: return launch_m<BITS, 32, BF>(L, A, pk, C, ws, s, (int)M);
-        default: return launch_m<BITS, 64, BF>(L, A, pk, C, ws, s, (int)M);
+        default: return launch_m<BITS, 32, BF>(L, A, pk, C, ws, s, (int)M);
     }
 }
 }  // namespace
 
 int launch_skinny_gemm(const Layout& L, const uint16_t* A, const void* packed, uint16_t* C,
                        int64_t M, void* ws, hipStream_t s, bool bf) {
-    if (M < 1 || M > kSkinnyMaxM) return TF_ERR_ARG;
+    if (M < 1 || M > kStreamMaxM) return TF_ERR_ARG;
     const uint8_t* pk = static_cast<const uint8_t*>(packed);
     if (bf)
         return L.bits == 4 ? launch_skinny_bits<4, true>(L, A, pk, C, M, ws, s)

@@ -49,9 +49,15 @@ constexpr int kLayoutVersion = 1;
 constexpr int64_t kWsCounterBytes = (TF_MAX_DIM / 32) * 4;
 // Most workgroups a stream-K GEMM launch uses (sizes its workspace).
 constexpr int kSkMaxGroups = 256;
-// GEMM calls with kSkinnyMinM..kSkinnyMaxM rows run the streaming kernel's
-// matrix-core form (16, 32 or 64 row slots); fewer rows run the decode GEMV.
+// GEMM calls with kSkinnyMinM..kStreamMaxM rows run the streaming kernel's
+// matrix-core form (16 or 32 row slots); fewer rows run the decode GEMV, more
+// the tiled GEMMs (from 33 rows the streaming kernel, every weight dequantized
+// for 64 row slots, is slower than one round of 64 x 64 tiles: K = 4096,
+// N = 14336, M = 33, 64 W4 17.4, 25.4 against 13.6, 14.8 us, W8 M = 64 46
+// against 17 us).  The workspace promised up to kSkinnyMaxM rows is the
+// streaming kernel's.
 constexpr int kSkinnyMinM = 4;
+constexpr int kStreamMaxM = 32;
 constexpr int kSkinnyMaxM = 64;
 constexpr int kAtomK = 32;
 constexpr int kAtomBytes = 1024;
@@ -550,12 +556,16 @@ int launch_skinny_gemm(const Layout& L, const uint16_t* A, const void* packed, u
                        int64_t M, void* ws, hipStream_t s, bool bf);
 int64_t gemm_workspace_bytes(const Layout& L, int64_t M);
 bool gemm256_supported(const Layout& L);
-bool gemm256_fills_device(const Layout& L, int64_t M, hipStream_t s);
 int64_t gemm256_workspace_bytes(const Layout& L, int64_t M);
+// Expected time in nanoseconds with ws_bytes of workspace on cus compute units.
+int64_t gemm256_cost(const Layout& L, int64_t M, int64_t ws_bytes, int64_t cus, bool bf);
 int launch_gemm256(const Layout& L, const uint16_t* A, const uint8_t* pk, uint16_t* C, int64_t M,
                    void* ws, size_t ws_bytes, hipStream_t s, bool bf);
-// The 64 x 128 GEMM with K split over the workgroup's waves (no workspace).
+// The 64 x 128 GEMM with K split over the workgroup's waves (no workspace),
+// and its expected time in nanoseconds (of one round: a tile of BN columns).
 bool gemm_ks_supported(const Layout& L);
+int64_t gemm_ks_round_cost(const Layout& L, bool wide, bool bf);
+int64_t gemm_ks_cost(const Layout& L, int64_t M, int64_t cus, bool bf);
 int launch_gemm_ks(const Layout& L, const uint16_t* A, const void* packed, uint16_t* C, int64_t M,
                    hipStream_t s, bool bf);
 // The same kernel over a range of the 256-row GEMM's 256 x 256 tiles: count
@@ -566,6 +576,11 @@ struct KsRange {
 };
 int launch_gemm_ks_range(const Layout& L, const uint16_t* A, const void* packed, uint16_t* C, int64_t M,
                          const KsRange& rg, hipStream_t s, bool bf);
+// The GEMM with tiles of 128 x 128 (rb = 8) or 64 x 64 (rb = 4), K in S slices
+// (S > 1 needs ws) and each slice split over the workgroup's waves; any K and
+// group.
+int launch_gemm_kq(const Layout& L, const uint16_t* A, const void* packed, uint16_t* C, int64_t M, int rb, int S,
+                   void* ws, hipStream_t s, bool bf);
 int launch_gemm(const Layout& L, const uint16_t* A, const void* packed, uint16_t* C, int64_t M,
                 void* ws, size_t ws_bytes, hipStream_t s, bool bf);
 int launch_silu_mul(const uint16_t* gu, int64_t M, int64_t N, uint16_t* h, hipStream_t s, bool bf);
