@@ -6,86 +6,131 @@
 namespace tf {
 namespace {
 
-// Row offset (0..7) held by nibble position j of a packed 4-bit dword.
-__device__ __forceinline__ int w4_row_of_nibble(int j) { return j < 4 ? 2 * j : 2 * (j - 4) + 1; }
+// Packing: a block of 256 threads rearranges one 32-row atom of each of 8
+// panels (512 4-bit or 256 8-bit columns), so that every row is read as 256
+// consecutive bytes, and, where the atom opens a group, the panels' scales and
+// zero-points.  Thread (kg, w) loads word w (8 4-bit or 4 8-bit columns) of
+// the 8 rows 8 kg .. 8 kg + 7 and transposes them in registers into the 8
+// dwords those codes have in the layout; LDS gathers the dwords of the atoms,
+// which leave as 16 bytes per lane, 1 KB in a row.
+// Bound by memory: K = 4096, N = 14336 4-bit moves 61 MB.  Measured on MI355X:
+// one thread per output dword, gathering its 8 codes with 4-byte loads, and a
+// second launch for the metadata took 31.9 us (1.9 TB/s), this form 12.2 us
+// (5.0 TB/s, the rate of a large copy).
+constexpr int kPackPanels = 8, kPackThreads = 256;
+constexpr int kPackStride = 256 + 4;     // dwords of LDS per atom: the panels' stores fall on different banks
 
-// One thread per output dword of the weights region.
-__global__ void pack_w4_weights(const int32_t* __restrict__ qw, uint32_t* __restrict__ out,
-                                int64_t K, int64_t N, int64_t na, int64_t total_dwords) {
-    int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= total_dwords) return;
-    int64_t atom = d >> 8;
-    int within = (int)(d & 255);
-    int lane = within >> 2, t = within & 3;
-    int64_t p = atom / na, a = atom % na;
-    int c = lane & 15, kg = lane >> 4;
-    int64_t n = p * 64 + c + 16 * t;
-    uint32_t word = 0;
-    if (n < N) {
-        int64_t k0 = a * kAtomK + 8 * kg;
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(qw);
-        int shift = 4 * (int)(n & 7);
-        for (int j = 0; j < 8; ++j) {
-            int64_t k = k0 + w4_row_of_nibble(j);
-            uint32_t q = (src[k * (N / 8) + (n >> 3)] >> shift) & 0xFu;
-            word |= q << (4 * j);
-        }
+struct PackMeta {
+    const uint16_t* sc;      // scales [ng, s_gstride] (s_gstride 0: one row for every group)
+    const uint8_t* z;        // zero-points as the caller has them (4-bit: packed words), or NULL
+    int64_t s_gstride;
+    int zconst;              // the zero-point where z is NULL
+    int64_t s_off, z_off;
+    int ng, apg;             // groups; atoms per group
+};
+
+// 8 x 8 transpose of nibbles: afterwards nibble j of v[i] is what was nibble i of v[j].
+__device__ __forceinline__ void transpose_nibbles(uint32_t (&v)[8]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t a = v[j], b = v[j + 4];
+        v[j] = __builtin_amdgcn_perm(b, a, 0x05040100u);
+        v[j + 4] = __builtin_amdgcn_perm(b, a, 0x07060302u);
     }
-    out[d] = word;
+#pragma unroll
+    for (int h = 0; h < 8; h += 4)
+#pragma unroll
+        for (int j = h; j < h + 2; ++j) {
+            const uint32_t a = v[j], b = v[j + 2];
+            v[j] = __builtin_amdgcn_perm(b, a, 0x06020400u);
+            v[j + 2] = __builtin_amdgcn_perm(b, a, 0x07030501u);
+        }
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+        const uint32_t a = v[j], b = v[j + 1];
+        v[j] = (a & 0x0F0F0F0Fu) | ((b << 4) & 0xF0F0F0F0u);
+        v[j + 1] = ((a >> 4) & 0x0F0F0F0Fu) | (b & 0xF0F0F0F0u);
+    }
+}
+// 4 x 4 transpose of bytes.
+__device__ __forceinline__ void transpose_bytes(uint32_t& r0, uint32_t& r1, uint32_t& r2, uint32_t& r3) {
+    const uint32_t a = __builtin_amdgcn_perm(r1, r0, 0x05010400u), b = __builtin_amdgcn_perm(r1, r0, 0x07030602u);
+    const uint32_t c = __builtin_amdgcn_perm(r3, r2, 0x05010400u), d = __builtin_amdgcn_perm(r3, r2, 0x07030602u);
+    r0 = __builtin_amdgcn_perm(c, a, 0x05040100u);
+    r1 = __builtin_amdgcn_perm(c, a, 0x07060302u);
+    r2 = __builtin_amdgcn_perm(d, b, 0x05040100u);
+    r3 = __builtin_amdgcn_perm(d, b, 0x07060302u);
 }
 
 // flip = 0x80808080 turns signed INT8 codes into unsigned codes q + 128
 // (two's complement: flipping the sign bit adds 128).
-__global__ void pack_w8_weights(const uint8_t* __restrict__ qw, uint32_t* __restrict__ out,
-                                int64_t K, int64_t N, int64_t na, int64_t total_dwords,
-                                uint32_t flip) {
-    int64_t d = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (d >= total_dwords) return;
-    int64_t atom = d >> 8;
-    int within = (int)(d & 255);
-    int lane = within >> 2, t = within & 3;
-    int64_t p = atom / na, a = atom % na;
-    int c = lane & 15, kg = lane >> 4;
-    int64_t n = p * 32 + c + 16 * (t >> 1);
-    uint32_t word = 0;
-    if (n < N) {
-        int64_t k0 = a * kAtomK + 8 * kg + 4 * (t & 1);
-        for (int b = 0; b < 4; ++b) word |= (uint32_t)qw[(k0 + b) * N + n] << (8 * b);
-        word ^= flip;
+template <int BITS>
+__global__ __launch_bounds__(kPackThreads) void pack_kernel(const uint32_t* __restrict__ qw, uint8_t* __restrict__ packed,
+                                                            int N, int np, int na, uint32_t flip, PackMeta mt) {
+    constexpr int PW = BITS == 4 ? 64 : 32, T = PW / 16;
+    constexpr int WPP = 8;                          // words of a row per panel
+    __shared__ __align__(16) uint32_t st[kPackPanels * kPackStride];
+    const int tid = threadIdx.x, w = tid & 63, kg = tid >> 6;
+    const int a = blockIdx.y;
+    const int64_t p0 = (int64_t)blockIdx.x * kPackPanels;
+    const int64_t row_words = (int64_t)N * BITS / 32, word = p0 * WPP + w;
+    // words past the row: the columns past N hold q = 0 (8-bit rows end on a
+    // word too, N % 8 == 0)
+    const bool in = word < row_words;
+    const uint32_t* src = qw + (int64_t)(a * kAtomK + 8 * kg) * row_words + word;
+    uint32_t v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        // 4-bit: nibble position j holds row offset 2 j or 2 (j - 4) + 1
+        const int r = BITS == 8 ? j : j < 4 ? 2 * j : 2 * (j - 4) + 1;
+        v[j] = in ? src[r * row_words] ^ flip : 0u;
     }
-    out[d] = word;
-}
-
-// One thread per metadata entry: scales copied bit for bit, zero-points
-// unpacked to one byte each.  s_gstride = N for per-group scales [K/G, N], 0
-// for one scale per column [N]; with neither zero-point array, zconst.
-__global__ void pack_meta(const uint16_t* __restrict__ sc, const int32_t* __restrict__ qz4,
-                          const uint8_t* __restrict__ z8, uint16_t* __restrict__ s_out,
-                          uint8_t* __restrict__ z_out, int64_t N, int64_t ng, int pw,
-                          int64_t entries, int64_t s_gstride, int zconst) {
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= entries) return;
-    int64_t p = e / (ng * pw);
-    int64_t g = (e / pw) % ng;
-    int i = (int)(e % pw);
-    int T = pw / 16;
-    int c = i / T, t = i % T;
-    int64_t n = p * pw + c + 16 * t;
-    uint16_t s = 0;
-    uint8_t z = 0;
-    if (n < N) {
-        s = sc[g * s_gstride + n];
-        if (qz4) {
-            uint32_t w = reinterpret_cast<const uint32_t*>(qz4)[g * (N / 8) + (n >> 3)];
-            z = (uint8_t)((w >> (4 * (int)(n & 7))) & 0xFu);
-        } else if (z8) {
-            z = z8[g * N + n];
-        } else {
-            z = (uint8_t)zconst;
+    uint32_t* const dst = st + (w / WPP) * kPackStride + kg * 64;
+    if constexpr (BITS == 4) {
+        transpose_nibbles(v);
+        // column 8 (w % 8) + i of the panel: c = 8 (w % 2) + i, t = (w % 8) / 2
+#pragma unroll
+        for (int i = 0; i < 8; ++i) dst[(8 * (w & 1) + i) * 4 + (w % 8) / 2] = v[i];
+    } else {
+        transpose_bytes(v[0], v[1], v[2], v[3]);
+        transpose_bytes(v[4], v[5], v[6], v[7]);
+        // column 4 (w % 8) + i: c = 4 (w % 4) + i, dwords 2 ((w % 8) / 4) + 0, 1 for rows 0..3, 4..7
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *reinterpret_cast<u32x2*>(&dst[(4 * (w & 3) + i) * 4 + 2 * ((w % 8) / 4)]) = u32x2{v[i], v[4 + i]};
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int pp = (tid >> 6) + 4 * h;          // panel of this wave's store
+        if (p0 + pp < np)
+            *reinterpret_cast<u32x4*>(packed + ((p0 + pp) * na + a) * kAtomBytes + 16 * w) =
+                *reinterpret_cast<const u32x4*>(&st[pp * kPackStride + 4 * w]);
+    }
+    // scales (copied bit for bit) and zero-points (a byte each) of the group this atom opens
+    if (a % mt.apg != 0) return;
+    const int64_t g = a / mt.apg;
+#pragma unroll
+    for (int h = 0; h < kPackPanels * PW / kPackThreads; ++h) {
+        const int col = tid + h * kPackThreads;
+        const int64_t p = p0 + col / PW, n = p0 * PW + col;
+        if (p >= np) break;
+        uint16_t s = 0;
+        uint8_t z = 0;
+        if (n < N) {
+            s = mt.sc[g * mt.s_gstride + n];
+            if (!mt.z)
+                z = (uint8_t)mt.zconst;
+            else if (BITS == 4)
+                z = (uint8_t)((mt.z[g * (N / 2) + n / 2] >> (4 * (n & 1))) & 0xFu);
+            else
+                z = mt.z[g * N + n];
         }
+        const int e = (col % 16) * T + col % PW / 16;        // entry c * T + t of column c + 16 t
+        const int64_t at = (p * mt.ng + g) * PW + e;
+        reinterpret_cast<uint16_t*>(packed + mt.s_off)[at] = s;
+        packed[mt.z_off + at] = z;
     }
-    s_out[e] = s;
-    z_out[e] = z;
 }
 
 // Column and row of code (lane, dword t, position j) of an atom.
@@ -212,30 +257,26 @@ inline unsigned blocks_for(int64_t n, int threads) { return (unsigned)((n + thre
 
 }  // namespace
 
+namespace {
+template <int BITS>
+int launch_pack(const void* qw, const void* z, const uint16_t* sc, int64_t s_gstride, int zconst, uint32_t flip,
+                const Layout& L, void* packed, hipStream_t s) {
+    const PackMeta mt{sc, static_cast<const uint8_t*>(z), s_gstride, zconst, L.s_off, L.z_off, (int)L.ng,
+                      L.group / kAtomK};
+    const dim3 grid((unsigned)((L.np + kPackPanels - 1) / kPackPanels), (unsigned)L.na);
+    return launch(pack_kernel<BITS>, grid, dim3(kPackThreads), 0, s, static_cast<const uint32_t*>(qw),
+                  static_cast<uint8_t*>(packed), (int)L.N, (int)L.np, (int)L.na, flip, mt);
+}
+}  // namespace
+
 int launch_pack_w4(const int32_t* qw, const int32_t* qz, const uint16_t* sc, const Layout& L,
                    void* packed, hipStream_t s) {
-    uint8_t* base = static_cast<uint8_t*>(packed);
-    int64_t dwords = L.np * L.na * 256;
-    int rc = launch(pack_w4_weights, dim3(blocks_for(dwords, 256)), dim3(256), 0, s, qw,
-                    reinterpret_cast<uint32_t*>(base + L.w_off), L.K, L.N, L.na, dwords);
-    if (rc) return rc;
-    int64_t entries = L.np * L.ng * L.pw;
-    return launch(pack_meta, dim3(blocks_for(entries, 256)), dim3(256), 0, s, sc, qz,
-                  (const uint8_t*)nullptr, reinterpret_cast<uint16_t*>(base + L.s_off),
-                  base + L.z_off, L.N, L.ng, (int)L.pw, entries, L.N, 0);
+    return launch_pack<4>(qw, qz, sc, L.N, 0, 0u, L, packed, s);
 }
 
 int launch_pack_w8(const uint8_t* qw, const uint8_t* zr, const uint16_t* sc, const Layout& L,
                    void* packed, hipStream_t s) {
-    uint8_t* base = static_cast<uint8_t*>(packed);
-    int64_t dwords = L.np * L.na * 256;
-    int rc = launch(pack_w8_weights, dim3(blocks_for(dwords, 256)), dim3(256), 0, s, qw,
-                    reinterpret_cast<uint32_t*>(base + L.w_off), L.K, L.N, L.na, dwords, 0u);
-    if (rc) return rc;
-    int64_t entries = L.np * L.ng * L.pw;
-    return launch(pack_meta, dim3(blocks_for(entries, 256)), dim3(256), 0, s, sc,
-                  (const int32_t*)nullptr, zr, reinterpret_cast<uint16_t*>(base + L.s_off),
-                  base + L.z_off, L.N, L.ng, (int)L.pw, entries, L.N, 0);
+    return launch_pack<8>(qw, zr, sc, L.N, 0, 0u, L, packed, s);
 }
 
 // Signed INT8 with one scale per column (Eq. 1): stored as the 8-bit layout
@@ -243,17 +284,7 @@ int launch_pack_w8(const uint8_t* qw, const uint8_t* zr, const uint16_t* sc, con
 // so s * ((q + 128) - 128) = s * q through the same kernels.
 int launch_pack_w8_sym(const int8_t* qw, const uint16_t* sc, const Layout& L, void* packed,
                        hipStream_t s) {
-    uint8_t* base = static_cast<uint8_t*>(packed);
-    int64_t dwords = L.np * L.na * 256;
-    int rc = launch(pack_w8_weights, dim3(blocks_for(dwords, 256)), dim3(256), 0, s,
-                    reinterpret_cast<const uint8_t*>(qw), reinterpret_cast<uint32_t*>(base + L.w_off),
-                    L.K, L.N, L.na, dwords, 0x80808080u);
-    if (rc) return rc;
-    int64_t entries = L.np * L.ng * L.pw;
-    return launch(pack_meta, dim3(blocks_for(entries, 256)), dim3(256), 0, s, sc,
-                  (const int32_t*)nullptr, (const uint8_t*)nullptr,
-                  reinterpret_cast<uint16_t*>(base + L.s_off), base + L.z_off, L.N, L.ng, (int)L.pw,
-                  entries, (int64_t)0, 128);
+    return launch_pack<8>(qw, nullptr, sc, 0, 128, 0x80808080u, L, packed, s);
 }
 
 int launch_unpack(const Layout& L, const void* packed, uint8_t* q_out, uint8_t* z_out,
