@@ -95,11 +95,37 @@ def build_probe() -> str:
     return PROBE_LIB
 
 
+BINDING_SRC = os.path.join(PKG, "binding", "tf_binding.cpp")
+BINDING = os.path.join(PKG, "_tf_binding.so")
+
+
+def build_binding() -> str:
+    """The native half of the Python binding (host code only: a CPython
+    extension over torch's C++ tensors, called from tilefuse.py)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    inc = [f"-I{d}" for d in cpp_extension.include_paths()] + [f"-I{sysconfig.get_paths()['include']}"]
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc, BINDING_SRC,
+           f"-L{lib}", "-lc10", "-ltorch_cpu", "-ltorch_python", f"-Wl,-rpath,{lib}", "-o", BINDING + ".tmp"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed for tf_binding.cpp:\n{r.stderr}")
+    os.replace(BINDING + ".tmp", BINDING)
+    return BINDING
+
+
 def build(verbose: bool = False) -> str:
-    _build_into(LIB)
-    build_probe()
+    with cf.ThreadPoolExecutor(1) as ex:
+        binding = ex.submit(build_binding)
+        _build_into(LIB)
+        build_probe()
+        binding.result()
     if verbose:
-        print(f"built {LIB} and {PROBE_LIB}")
+        print(f"built {LIB}, {BINDING} and {PROBE_LIB}")
     return LIB
 
 

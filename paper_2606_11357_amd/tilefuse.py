@@ -188,7 +188,42 @@ def pack_w8_sym(qweight, scales, K: int, N: int, group: int = 128, out=None):
     return out
 
 
+_bound = None
+
+
+def _native():
+    """The native module's matmul, bound to the loaded library's functions."""
+    global _bound
+    if _bound is None:
+        torch = _torch()
+        lib = load()
+        try:
+            from . import _tf_binding
+        except ImportError as e:
+            raise ImportError("the native binding is missing or does not load; build it with "
+                              "`python -m paper_2606_11357_amd.build`") from e
+        at = lambda name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value  # noqa: E731
+        fns = tuple(at(f"tf_w{bits}a16_{kind}{dt}") for bits in (4, 8) for kind in ("gemm", "gemv")
+                    for dt in ("", "_bf16"))
+        stream = torch._C._cuda_getCurrentRawStream
+        _tf_binding.bind(fns, at("tf_workspace_bytes"), stream, _default_ws, default_workspace)
+        _bound = _tf_binding.matmul
+    return _bound
+
+
 def _matmul(bits, kind, A, packed, K, N, group, out, workspace):
+    # The common form in one native call (a decode loop would otherwise wait
+    # for the steps below); any other form, and every refusal, comes back as
+    # NotImplemented and takes them.
+    got = (_bound or _native())(bits, kind == "gemv", A, packed, K, N, group, out, workspace)
+    if type(got) is int:
+        _check(got, f"tf_w{bits}a16_{kind}" + ("_bf16" if A.dtype == _torch().bfloat16 else ""))
+    if got is not NotImplemented:
+        return got
+    return _matmul_general(bits, kind, A, packed, K, N, group, out, workspace)
+
+
+def _matmul_general(bits, kind, A, packed, K, N, group, out, workspace):
     """A fp16 or bfloat16 [M, K] selects the entry point (the packed scales must
     hold the same dtype's bits); the output has A's dtype.
     workspace: None -> the cached per-device default, False -> none (single-pass

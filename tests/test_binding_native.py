@@ -1,0 +1,90 @@
+"""The native half of the Python binding against the general path it stands
+for: the same output tensors and bits in every accepted form, the same
+exception for every refused one (a form that the native call does not take
+comes back and runs through the general path)."""
+from __future__ import annotations
+
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2606_11357_amd import tilefuse as T  # noqa: E402
+
+K, N = 4096, 1024      # 64 rows or fewer split K through a workspace
+
+
+def _raised(f, *a, **kw):
+    try:
+        f(*a, **kw)
+    except Exception as e:   # noqa: BLE001
+        return type(e), str(e)
+    return None
+
+
+def _cpu(*shape, dtype=torch.float16):
+    return torch.zeros(shape, dtype=dtype)
+
+
+def _refusals(x, packed):
+    """(A, packed, K, N, group, out, workspace) the binding refuses."""
+    half = x.dtype
+    dev = x.device
+    return [
+        (x.float(), packed, K, N, 128, None, None),
+        (x[0], packed, K, N, 128, None, None),
+        (x, packed, K - 128, N, 128, None, None),
+        (x.t().contiguous().t(), packed, K, N, 128, None, None),
+        (x, packed, K, N, 128, torch.empty((1, N), dtype=half, device=dev), None),
+        (x, packed, K, N, 128, torch.empty((x.shape[0], N), dtype=torch.float32, device=dev), None),
+        (x, packed, K, N, 100, None, None),
+        (x, packed, K, N + 4, 128, None, None),
+        (x, packed, K, N, 2 ** 40, None, False),
+        (x, packed, float(K), N, 128, None, None),
+        (x, packed, K, N, 128, None, torch.zeros(16, dtype=torch.uint8)),
+        (x, None, K, N, 128, None, False),
+        (x[:0], packed, K, N, 128, None, False),
+    ]
+
+
+def test_cpu_tensors_are_refused_alike():
+    x, packed = _cpu(4, K), _cpu(1024, dtype=torch.uint8)
+    for args in _refusals(x, packed) + [(x, packed, K, N, 128, None, None)]:
+        got = _raised(T._matmul, 4, "gemm", *args)
+        assert got is not None and got == _raised(T._matmul_general, 4, "gemm", *args)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
+def test_forms_match_the_general_path(dt):
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    words = lambda rows: torch.randint(-2 ** 31, 2 ** 31, (rows, N // 8), dtype=torch.int32, device="cuda",  # noqa: E731
+                                       generator=gen)
+    s = (0.01 * torch.rand((K // 128, N), device="cuda", generator=gen)).to(dt)
+    packed = T.pack_w4(words(K), words(K // 128), s, K, N)
+    for M, kind in ((1, "gemv"), (8, "gemv"), (16, "gemm"), (40, "gemm"), (300, "gemm")):
+        x = torch.randn((M, K), device="cuda", generator=gen).to(dt)
+        own = torch.zeros(max(256, T.workspace_bytes(4, M, K, N)), dtype=torch.uint8, device="cuda")
+        for ws in (None, False, own):
+            want = T._matmul_general(4, kind, x, packed, K, N, 128, None, ws)
+            got = T._matmul(4, kind, x, packed, K, N, 128, None, ws)
+            out = torch.empty_like(want)
+            assert T._matmul(4, kind, x, packed, K, N, 128, out, ws) is out
+            side = torch.cuda.Stream()
+            side.wait_stream(torch.cuda.current_stream())
+            with torch.cuda.stream(side):
+                there = T._matmul(4, kind, x, packed, K, N, 128, None, own)
+            torch.cuda.current_stream().wait_stream(side)
+            torch.cuda.synchronize()
+            assert got.dtype == dt and got.shape == (M, N) and not got.requires_grad
+            assert torch.equal(got, want) and torch.equal(out, want)
+            if ws is own:
+                assert torch.equal(there, want)
+        for args in _refusals(x, packed):
+            got = _raised(T._matmul, 4, kind, *args)
+            assert got == _raised(T._matmul_general, 4, kind, *args), args[2:5]
+    # a workspace smaller than the call needs is refused by the library
+    need = T.workspace_bytes(4, 40, K, N)
+    small = torch.zeros(need - 16, dtype=torch.uint8, device="cuda")
+    x = torch.zeros((40, K), dtype=dt, device="cuda")
+    with pytest.raises(T.TileFuseError):
+        T._matmul(4, "gemm", x, packed, K, N, 128, None, small)
