@@ -144,7 +144,7 @@ __device__ __forceinline__ int sk_begin(int v, int G, int U) { return (int)((int
 // Slots of a K step's 64 that carry dequantization micro-steps: two windows,
 // [W, 32) and [W + 32, 64), after the two LDS read bursts (slots 0..7 and
 // 32..39) have returned.  fp16 (52 or 48 micro-steps) uses W = 16, one or two
-// per slot; bf16 (92 or 80) uses W = 8, at most two per slot.
+// per slot; bf16 (76 or 80) uses W = 8, at most two per slot.
 template <bool BF>
 constexpr int dq_window() { return BF ? 8 : 16; }
 template <bool BF>

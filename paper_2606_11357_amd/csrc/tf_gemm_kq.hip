@@ -19,7 +19,7 @@
 //  - A step's MFMAs run column block by column block; while the RB MFMAs of
 //    block u run, the wave dequantizes (Eq. 2, rounded once, the code of the
 //    other GEMMs) the B operand of block u + 1.  With RB = 8 an operand of 13
-//    (bf16: 23) vector instructions covers eight MFMAs, half of what the
+//    (bf16: 19) vector instructions covers eight MFMAs, half of what the
 //    64-row tiles of gemm_ks_kernel pay per MFMA.
 //  - K need only be a multiple of 32 and a group of 32: steps are dealt to
 //    the waves in pairs, the last one to three steps of a run follow the loop,
@@ -37,7 +37,7 @@
 // 333 x 1376 x 2048 groups of 32 (a 128 x 128 kernel for any group, single
 // buffered) 33.9 -> 8.6; 64 x 4096 x 14336 (streaming form) 25.4 -> 12.8, W8
 // 46 -> 17; 200 x 14336 x 4096 (128 x 256 tiles, split K) 47.8 -> 33.2;
-// bf16 512 x 4096 x 14336 (64 x 256 tiles) 78 -> 62.5.
+// bf16 512 x 4096 x 14336 (64 x 256 tiles) 78 -> 61.4.
 #include <algorithm>
 
 #include "tf_internal.h"
