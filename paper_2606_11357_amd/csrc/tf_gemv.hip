@@ -79,7 +79,7 @@ struct WaveStage {
 // SEG > 0: segments (atoms summed before the scale is applied) have SEG
 // atoms, fixed at compile time (one group of 32 SEG rows); SEG = 0: group
 // size known at run time.  D: weight atoms a wave keeps in flight; D = U is
-// the one-round form (the vector forms with at most U atoms per wave): every
+// the one-round form (at most U atoms per wave; the matrix-core form: U): every
 // atom of the run is requested at the start and nothing is refilled.  CH: the
 // workgroups that share one panel (vector forms, all of K each): workgroup
 // part h computes the columns c + 16 t with t in [h T / CH, (h + 1) T / CH),
@@ -100,7 +100,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
     constexpr int MB = Cfg::MB;
     static_assert(SEG == 0 || U % SEG == 0, "segments tile a round");
     static_assert(U % D == 0, "the load ring tiles a round");
-    constexpr bool ONE = D == U && !MF;
+    constexpr bool ONE = D == U;
     static_assert(CH == 1 || (!MF && T % CH == 0), "column parts split a lane's columns");
     constexpr int TE = T / CH;                          // columns a lane computes
     // metadata of the groups one round touches: U / SEG groups, or up to U
@@ -336,7 +336,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
 #pragma unroll
                 for (int b = 0; b < MB; ++b) {
                     afrag[b] = aring[b][i % D];
-                    aring[b][i % D] = load_afrag(b, j + D);
+                    if constexpr (!ONE) aring[b][i % D] = load_afrag(b, j + D);
                 }
             }
             if constexpr (MF) {
@@ -675,6 +675,13 @@ int launch_g(const Layout& L, const uint16_t* A, const uint8_t* pk, uint16_t* C,
         if (sp.CH == 2) return with_parts(std::integral_constant<int, 2>{});
         return with_parts(std::integral_constant<int, 1>{});
     }
+    // matrix-core form: the one-round form where a wave's run fills its round
+    // (K just up to 2048 with eight waves); a shorter run would wait for
+    // repeated requests.  Measured (fp16, us, ring -> one round): K = 2048, M = 16,
+    // 32 W4 N = 2048 5.66, 8.3 -> 5.48, 7.7, N = 16384 7.05, 10.1 -> 6.4, 9.0, W8
+    // N = 2048 6.2, 8.8 -> 5.3, 7.3; runs of 6 and 4 atoms (K = 1376, 1024) 5.68 and
+    // 4.87 -> 6.04 and 5.33, left on the ring.
+    if (RW == kGemvU) return go(gemv_kernel<BITS, M, WAVES, SEG, kGemvU, BF, 1>, kGemvU, 1);
     return go(gemv_kernel<BITS, M, WAVES, SEG, gemv_ring_for(M), BF, 1>, gemv_ring_for(M), 1);
 }
 
