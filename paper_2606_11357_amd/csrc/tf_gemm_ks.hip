@@ -557,11 +557,13 @@ bool gemm_ks_supported(const Layout& L) {
 }
 
 // Measured rounds (see the choice of kernel in tf_gemm.hip): 64 x 128 tiles at
-// K = 2048, 4096, 14336 11.5, 19, 49 us in fp16, 13.7, 22.5, 62 in bf16;
-// 64 x 256 at K = 4096 34.4 and 40.4 us.
+// K = 2048, 4096 11.5, 19 us in fp16, 13.7, 22.5 in bf16; with long K 49 (bf16 62)
+// us at K = 14336 while half the compute units work, 62 on all of them and at
+// K = 11008 in two rounds; 64 x 256 at K = 4096, 14336 34.4, 113 and 40.4, 123 us.
 int64_t gemm_ks_round_cost(const Layout& L, bool wide, bool bf) {
-    if (wide) return bf ? 11000 + 7200 * L.K / 1000 : 9500 + 6100 * L.K / 1000;
-    return 6000 + (bf ? 4000 : 3100) * L.K / 1000;
+    if (wide) return bf ? 7300 + 8070 * L.K / 1000 : 3300 + 7600 * L.K / 1000;
+    const int64_t per_k = L.K > 8192 ? (bf ? 5200 : 4300) : (bf ? 4000 : 3100);
+    return 6000 + per_k * L.K / 1000;
 }
 int64_t gemm_ks_cost(const Layout& L, int64_t M, int64_t cus, bool bf) {
     const bool wide = gemm_ks_wide(L, M, cus);
