@@ -68,9 +68,7 @@ const at::Tensor* plain(PyObject* o) {
     return t.is_cuda() && t.layout() == at::kStrided && t.is_contiguous() ? &t : nullptr;
 }
 
-// matmul(bits, gemv, A, packed, K, N, group, out, workspace): the output, the
-// library's status if it is not 0, or NotImplemented.
-PyObject* matmul(PyObject*, PyObject* const* a, Py_ssize_t n) {
+PyObject* matmul_common(PyObject* const* a, Py_ssize_t n) {
     if (n != 9 || !g_bytes) return not_here();
     for (const int i : {0, 4, 5, 6})
         if (!PyLong_CheckExact(a[i])) return not_here();
@@ -90,65 +88,73 @@ PyObject* matmul(PyObject*, PyObject* const* a, Py_ssize_t n) {
     const int64_t M = A->size(0);
     const int dev = A->get_device();
     PyObject *out_o = a[7], *ws_o = a[8];
-    try {
-        // the workspace: False none, None the device's cached one, or the caller's
-        Held held;                       // the cached workspace, over the call
-        void* ws = nullptr;
-        size_t ws_bytes = 0;
-        if (ws_o == Py_None) {
-            const int64_t need = g_bytes((int)bits, M, K, N, (int)group);
-            if (need < 0) return not_here();
-            if (need > 0) {
-                const Held key{PyLong_FromLong(dev)};
-                if (!key.o) return nullptr;
-                held.o = Py_XNewRef(PyDict_GetItemWithError(g_workspaces, key.o));
-                if (!held.o && PyErr_Occurred()) return nullptr;
-                const at::Tensor* t = held.o ? plain(held.o) : nullptr;
-                if (!t || t->numel() < need) {
-                    const Held device{PyObject_GetAttrString(a[2], "device")};
-                    if (!device.o) return nullptr;
-                    Py_XSETREF(held.o, PyObject_CallFunction(g_workspace, "OL", device.o, (long long)need));
-                    if (!held.o) return nullptr;
-                    t = plain(held.o);
-                    if (!t) return not_here();
-                }
-                ws = t->data_ptr();
-                ws_bytes = t->nbytes();
+    // the workspace: False none, None the device's cached one, or the caller's
+    Held held;                       // the cached workspace, over the call
+    void* ws = nullptr;
+    size_t ws_bytes = 0;
+    if (ws_o == Py_None) {
+        const int64_t need = g_bytes((int)bits, M, K, N, (int)group);
+        if (need < 0) return not_here();
+        if (need > 0) {
+            const Held key{PyLong_FromLong(dev)};
+            if (!key.o) return nullptr;
+            held.o = Py_XNewRef(PyDict_GetItemWithError(g_workspaces, key.o));
+            if (!held.o && PyErr_Occurred()) return nullptr;
+            const at::Tensor* t = held.o ? plain(held.o) : nullptr;
+            if (!t || t->numel() < need) {
+                const Held device{PyObject_GetAttrString(a[2], "device")};
+                if (!device.o) return nullptr;
+                Py_XSETREF(held.o, PyObject_CallFunction(g_workspace, "OL", device.o, (long long)need));
+                if (!held.o) return nullptr;
+                t = plain(held.o);
+                if (!t) return not_here();
             }
-        } else if (ws_o != Py_False) {
-            const at::Tensor* t = plain(ws_o);
-            if (!t) return not_here();
             ws = t->data_ptr();
             ws_bytes = t->nbytes();
         }
-        at::Tensor made;
-        const at::Tensor* out;
-        if (out_o == Py_None) {
-            made = at::empty({M, N}, A->options().requires_grad(false));
-            out = &made;
-        } else {
-            out = plain(out_o);
-            if (!out || out->scalar_type() != A->scalar_type() || out->dim() != 2 || out->size(0) != M ||
-                out->size(1) != N)
-                return not_here();
-        }
-        const Held index{PyLong_FromLong(dev)};
-        const Held handle{index.o ? PyObject_CallOneArg(g_stream, index.o) : nullptr};
-        if (!handle.o) return nullptr;
-        void* stream = PyLong_AsVoidPtr(handle.o);
-        const MatmulFn fn = g_fn[(bits == 8 ? 4 : 0) + (gemv ? 2 : 0) + (bf ? 1 : 0)];
-        const uint16_t* x = static_cast<const uint16_t*>(A->data_ptr());
-        const void* pk = packed->data_ptr();
-        uint16_t* y = static_cast<uint16_t*>(out->data_ptr());
-        int rc;
-        Py_BEGIN_ALLOW_THREADS;
-        rc = fn(x, pk, y, M, K, N, (int)group, ws, ws_bytes, stream);
-        Py_END_ALLOW_THREADS;
-        if (rc != 0) return PyLong_FromLong(rc);
-        return out_o == Py_None ? THPVariable_Wrap(std::move(made)) : Py_NewRef(out_o);
-    } catch (const std::exception&) {
-        // nothing has been launched: the general path meets the same condition
-        // (memory that is not there) and raises it as torch does
+    } else if (ws_o != Py_False) {
+        const at::Tensor* t = plain(ws_o);
+        if (!t) return not_here();
+        ws = t->data_ptr();
+        ws_bytes = t->nbytes();
+    }
+    at::Tensor made;
+    const at::Tensor* out;
+    if (out_o == Py_None) {
+        made = at::empty({M, N}, A->options().requires_grad(false));
+        out = &made;
+    } else {
+        out = plain(out_o);
+        if (!out || out->scalar_type() != A->scalar_type() || out->dim() != 2 || out->size(0) != M ||
+            out->size(1) != N)
+            return not_here();
+    }
+    const Held index{PyLong_FromLong(dev)};
+    const Held handle{index.o ? PyObject_CallOneArg(g_stream, index.o) : nullptr};
+    if (!handle.o) return nullptr;
+    void* stream = PyLong_AsVoidPtr(handle.o);
+    const MatmulFn fn = g_fn[(bits == 8 ? 4 : 0) + (gemv ? 2 : 0) + (bf ? 1 : 0)];
+    const uint16_t* x = static_cast<const uint16_t*>(A->data_ptr());
+    const void* pk = packed->data_ptr();
+    uint16_t* y = static_cast<uint16_t*>(out->data_ptr());
+    int rc;
+    Py_BEGIN_ALLOW_THREADS;
+    rc = fn(x, pk, y, M, K, N, (int)group, ws, ws_bytes, stream);
+    Py_END_ALLOW_THREADS;
+    if (rc != 0) return PyLong_FromLong(rc);
+    return out_o == Py_None ? THPVariable_Wrap(std::move(made)) : Py_NewRef(out_o);
+}
+
+// matmul(bits, gemv, A, packed, K, N, group, out, workspace): the output, the
+// library's status if it is not 0, or NotImplemented.
+PyObject* matmul(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    // No exception leaves a C entry.  Any access to a tensor may throw (a nested
+    // tensor with rows of different lengths has no size(1); memory may be short),
+    // and none follows the launch but the wrapping of the output: the general path
+    // meets the same condition and raises it as torch does.
+    try {
+        return matmul_common(a, n);
+    } catch (...) {
         return PyErr_Occurred() ? nullptr : not_here();
     }
 }

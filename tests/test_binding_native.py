@@ -4,11 +4,18 @@ exception for every refused one (a form that the native call does not take
 comes back and runs through the general path)."""
 from __future__ import annotations
 
+import os
+import subprocess
+import sys
+
 import pytest
 
 torch = pytest.importorskip("torch")
 
+from paper_2606_11357_amd import build as B  # noqa: E402
 from paper_2606_11357_amd import tilefuse as T  # noqa: E402
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 K, N = 4096, 1024      # 64 rows or fewer split K through a workspace
 
@@ -43,7 +50,16 @@ def _refusals(x, packed):
         (x, packed, K, N, 128, None, torch.zeros(16, dtype=torch.uint8)),
         (x, None, K, N, 128, None, False),
         (x[:0], packed, K, N, 128, None, False),
+        (_ragged(x), packed, K, N, 128, None, None),
+        (x, packed, K, N, 128, _ragged(x), None),
     ]
+
+
+def _ragged(x):
+    """A nested tensor (exactly torch.Tensor, strided) whose rows differ in
+    length: asking it for its second size raises."""
+    return torch.nested.nested_tensor([torch.zeros(K, dtype=x.dtype), torch.zeros(K // 2, dtype=x.dtype)],
+                                      device=x.device)
 
 
 def test_cpu_tensors_are_refused_alike():
@@ -51,6 +67,34 @@ def test_cpu_tensors_are_refused_alike():
     for args in _refusals(x, packed) + [(x, packed, K, N, 128, None, None)]:
         got = _raised(T._matmul, 4, "gemm", *args)
         assert got is not None and got == _raised(T._matmul_general, 4, "gemm", *args)
+
+
+def test_no_exception_leaves_the_native_call(tmp_path, monkeypatch):
+    """The native call's own source, built without its test for the device, on
+    CPU tensors whose sizes raise when asked for: they come back as
+    NotImplemented (an exception that left the C entry would end the process)."""
+    with open(B.BINDING_SRC) as f:
+        text = f.read()
+    assert text.count("t.is_cuda() && ") == 1
+    src = tmp_path / "tf_binding.cpp"
+    src.write_text(text.replace("t.is_cuda() && ", ""))
+    monkeypatch.setattr(B, "BINDING_SRC", str(src))
+    monkeypatch.setattr(B, "BINDING", str(tmp_path / "_tf_binding.so"))
+    B.build_binding()
+    script = """
+import sys; sys.path.insert(0, %r)
+import torch, _tf_binding as native
+from test_binding_native import _ragged, K, N
+native.bind((1,) * 8, 1, None, {}, None)      # addresses that no call below reaches
+x, packed = torch.zeros(2, K, dtype=torch.float16), torch.zeros(64, dtype=torch.uint8)
+r = _ragged(x)
+for args in ((r, packed, K, N, 128, None, False), (x, packed, K, N, 128, r, False)):
+    assert native.matmul(4, False, *args) is NotImplemented
+print("done")
+""" % str(tmp_path)
+    env = dict(os.environ, PYTHONPATH=os.pathsep.join([ROOT, os.path.join(ROOT, "tests")]))
+    r = subprocess.run([sys.executable, "-c", script], cwd=ROOT, env=env, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "done" in r.stdout, r.stderr[-3000:]
 
 
 @pytest.mark.gpu
