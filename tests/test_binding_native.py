@@ -97,6 +97,36 @@ print("done")
     assert r.returncode == 0 and "done" in r.stdout, r.stderr[-3000:]
 
 
+def _without_native(monkeypatch):
+    """As if the native module were not built."""
+    monkeypatch.setitem(sys.modules, f"{T.__package__}._tf_binding", None)
+    monkeypatch.delattr(sys.modules[T.__package__], "_tf_binding", raising=False)
+    monkeypatch.setattr(T, "_bound", None)
+
+
+def test_without_the_native_module_calls_take_the_general_path(monkeypatch):
+    _without_native(monkeypatch)
+    x, packed = _cpu(4, K), _cpu(1024, dtype=torch.uint8)
+    with pytest.warns(RuntimeWarning, match="native binding"):
+        got = _raised(T.w4a16_gemm, x, packed, K, N)
+    assert got == _raised(T._matmul_general, 4, "gemm", x, packed, K, N, 128, None, None)
+    assert got[0] is ValueError
+
+
+@pytest.mark.gpu
+def test_without_the_native_module_results_are_the_same(monkeypatch):
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    q, z = (torch.randint(0, 256, (rows, N), dtype=torch.uint8, device="cuda", generator=gen) for rows in (K, K // 128))
+    s = (0.001 * torch.rand((K // 128, N), device="cuda", generator=gen)).half()
+    packed = T.pack_w8(q, z, s, K, N)
+    x = torch.randn((3, K), device="cuda", generator=gen).half()
+    want = T.w8a16_gemv(x, packed, K, N)
+    _without_native(monkeypatch)
+    with pytest.warns(RuntimeWarning, match="native binding"):
+        got = T.w8a16_gemv(x, packed, K, N)
+    assert torch.equal(got, want)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dt", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
 def test_forms_match_the_general_path(dt):
