@@ -657,7 +657,8 @@ int launch_g(const Layout& L, const uint16_t* A, const uint8_t* pk, uint16_t* C,
             log_plan("gemv_kernel<%d,%d,%d,%d,%d,%s,%d> rows=%d K=%lld N=%lld G=%d: %s form, %lld panels x %d "
                      "column parts x %d K slices of %d atoms, %d atoms per wave%s", BITS, M, WAVES, SEG, d,
                      BF ? "bf16" : "f16", ch, mr, (long long)L.K, (long long)L.N, L.group,
-                     M > TF_GEMV_MAX_M ? "matrix-core" : (d == kGemvU ? "one-round vector" : "vector"),
+                     M > TF_GEMV_MAX_M ? (d == kGemvU ? "one-round matrix-core" : "matrix-core")
+                                       : (d == kGemvU ? "one-round vector" : "vector"),
                      (long long)L.np, ch, S, AS, RW, split ? ", partials summed by the last slice" : "");
         // column parts: whole groups of 8 ch workgroups (those past the last panel end at once)
         const int64_t gx = ch == 1 ? L.np : (L.np + 7) / 8 * 8 * ch;
@@ -676,12 +677,19 @@ int launch_g(const Layout& L, const uint16_t* A, const uint8_t* pk, uint16_t* C,
         return with_parts(std::integral_constant<int, 1>{});
     }
     // matrix-core form: the one-round form where a wave's run fills its round
-    // (K just up to 2048 with eight waves); a shorter run would wait for
-    // repeated requests.  Measured (fp16, us, ring -> one round): K = 2048, M = 16,
-    // 32 W4 N = 2048 5.66, 8.3 -> 5.48, 7.7, N = 16384 7.05, 10.1 -> 6.4, 9.0, W8
-    // N = 2048 6.2, 8.8 -> 5.3, 7.3; runs of 6 and 4 atoms (K = 1376, 1024) 5.68 and
-    // 4.87 -> 6.04 and 5.33, left on the ring.
-    if (RW == kGemvU) return go(gemv_kernel<BITS, M, WAVES, SEG, kGemvU, BF, 1>, kGemvU, 1);
+    // (K from 1793 to 2048, with groups of 128 from 1025, or such slices of it); a shorter one would wait
+    // for repeated requests (runs of 6 and 4 atoms, K = 1376, 1024, 5.68 and 4.87 ->
+    // 6.04 and 5.33 us) and stays on the ring.  It pays where a workgroup waits for
+    // its stream: measured (M = 4 .. 32, us, ring -> one round) W4 groups of 128
+    // K = 2048, N = 2048 M = 16, 32 5.66, 8.3 -> 5.48, 7.7, 16384 x 2048 (8 slices)
+    // 2-6% faster, W8 K = 2048, N = 2048 6.2, 8.8 -> 5.3, 7.3.  Closing a group costs vector
+    // work, and with a group each 32 rows of 4-bit codes that sets the time and
+    // asking for everything first only delays the first atom: 3% (16 slots) and 8%
+    // (32) slower at every N, so those keep the ring; 4-bit groups of 64 and 96 and 8-bit groups
+    // of 32 lose 1-8% on few workgroups and gain 0-20% from 128 on.
+    const bool one_round = RW == kGemvU && (L.group >= (BITS == 8 ? 64 : 128) ||
+                                            (L.np * S >= 128 && L.group >= (BITS == 8 ? 32 : 64)));
+    if (one_round) return go(gemv_kernel<BITS, M, WAVES, SEG, kGemvU, BF, 1>, kGemvU, 1);
     return go(gemv_kernel<BITS, M, WAVES, SEG, gemv_ring_for(M), BF, 1>, gemv_ring_for(M), 1);
 }
 
