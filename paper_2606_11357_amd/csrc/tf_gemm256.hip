@@ -721,19 +721,39 @@ Gemm256Plan plan_gemm256(const Layout& L, int64_t M, int64_t ws_bytes, int cus) 
 }
 }  // namespace
 
-// Measured: a whole tile 8 us and 20 ns per row of K (K = 4096: 90 us a
-// round); stream-K 26 us (refills, parked partials, the reduction launch) and
-// 21 ns per row of K that a block computes (K = 14336, N = 4096, M = 256, 1024,
-// 2048: 48, 108, 182 us).
-int64_t gemm256_cost(const Layout& L, int64_t M, int64_t ws_bytes, int64_t cus, bool bf) {
+// Expected time (fitted with the model of the other kernels, see tiled_cost;
+// within 3% for whole tiles, 8% for stream-K in two of three cases).  Whole
+// tiles: 9.2 us a round and 22 to 24 ns per row of K, less of it in a last round
+// that leaves units idle (K = 4096: 90 us a round).  Stream-K: 38 us where every block has a
+// part (refills, parked partials, the reduction launch) and the rows of K a
+// block computes (K = 14336, N = 4096, M = 256, 1024, 2048: 48, 108, 182 us).
+double gemm256_cost(const Layout& L, int64_t M, int64_t ws_bytes, int64_t cus, bool bf) {
     const Gemm256Plan p = plan_gemm256(L, M, ws_bytes, (int)cus);
     const int64_t tiles = ((M + kBM - 1) / kBM) * ((L.N + kBN - 1) / kBN);
-    if (p.sk.groups == 0) return (tiles + cus - 1) / cus * (8000 + 20 * L.K);
-    if (p.rest.count > 0)
-        return p.sk.dp_rounds * (8000 + 20 * L.K) +
-               (8 * p.rest.count + cus - 1) / cus * gemm_ks_round_cost(L, false, bf);
-    const int64_t chunks = L.K / (kBK * kCS);
-    return 26000 + 21 * kBK * kCS * (p.sk.dp_rounds * chunks + p.sk.units / p.sk.groups);
+    const int i = (L.bits == 8 ? 2 : 0) + (bf ? 1 : 0);
+    const bool whole_groups = L.group % (kBK * kCS) == 0;
+    const double k = (double)L.K * 1e-3;
+    if (p.sk.groups == 0) {
+        constexpr double kPer[4] = {21.7, 22.0, 23.7, 23.2};
+        const int64_t full = (tiles - 1) / cus;
+        const double idle = 1.0 - (double)(tiles - full * cus) / (double)cus;
+        return 1.9 + (double)(full + 1) * 9.2 +
+               ((double)(full + 1) - 0.35 * idle) * kPer[i] * (whole_groups ? 1.0 : 1.03) * k;
+    }
+    const double rounds = (double)p.sk.dp_rounds;
+    if (p.rest.count > 0) {
+        constexpr double kPer[4] = {20.7, 19.9, 22.2, 21.7};
+        return 4.0 + rounds * (11.9 + kPer[i] * (whole_groups ? 1.0 : 1.035) * k) +
+               (double)((8 * p.rest.count + cus - 1) / cus) * gemm_ks_round_cost(L, bf);
+    }
+    // rows of K, in thousands, of the stream-K part of a block
+    const double part = (double)((p.sk.units + p.sk.groups - 1) / p.sk.groups) * (kBK * kCS) * 1e-3;
+    if (p.sk.dp_rounds == 0) {
+        constexpr double kPer[4] = {20.9, 21.0, 23.0, 23.0};
+        return 2.1 + 38.0 * (double)p.sk.groups / (double)cus + kPer[i] * (whole_groups ? 1.0 : 1.1) * part;
+    }
+    constexpr double kPer[4] = {20.0, 19.8, 22.7, 21.3};
+    return 37.7 + rounds * 11.9 + kPer[i] * (whole_groups ? 1.0 : 1.08) * (rounds * k + 1.18 * part);
 }
 
 int launch_gemm256(const Layout& L, const uint16_t* A, const uint8_t* pk, uint16_t* C, int64_t M,

@@ -556,19 +556,22 @@ bool gemm_ks_supported(const Layout& L) {
     return L.K % chunk_rows == 0 && L.K / chunk_rows >= kKsWaves && (L.group & (L.group - 1)) == 0;
 }
 
-// Measured rounds (see the choice of kernel in tf_gemm.hip): 64 x 128 tiles at
-// K = 2048, 4096 11.5, 19 us in fp16, 13.7, 22.5 in bf16; with long K 49 (bf16 62)
-// us at K = 14336 while half the compute units work, 62 on all of them and at
-// K = 11008 in two rounds; 64 x 256 at K = 4096, 14336 34.4, 113 and 40.4, 123 us.
-int64_t gemm_ks_round_cost(const Layout& L, bool wide, bool bf) {
-    if (wide) return bf ? 7300 + 8070 * L.K / 1000 : 3300 + 7600 * L.K / 1000;
-    const int64_t per_k = L.K > 8192 ? (bf ? 5200 : 4300) : (bf ? 4000 : 3100);
-    return 6000 + per_k * L.K / 1000;
+// Expected time (see tiled_cost for the model and its error).  Some of the
+// timings behind it (us): 64 x 128 tiles at a full round of K = 2048, 4096 11.5,
+// 19 in fp16, 13.7, 22.5 in bf16; K = 14336 49 (bf16 62) while half the compute
+// units work, 62 on all of them; 64 x 256 at K = 4096, 14336 34.4, 113 and 40.4, 123.
+static constexpr TileCost kKs128{1.9, 4.4, 1.02, 6.2, 0.31, 4.7, {4.04, 4.68, 4.62, 5.17}};
+static constexpr TileCost kKs256{2.5, 7.2, 1.06, 10.0, 0.38, 7.6, {7.60, 8.59, 0.0, 0.0}};   // 4-bit weights only
+double gemm_ks_round_cost(const Layout& L, bool bf) {
+    return kKs128.round + kKs128.per_k[(L.bits == 8 ? 2 : 0) + (bf ? 1 : 0)] * (double)L.K * 1e-3;
 }
-int64_t gemm_ks_cost(const Layout& L, int64_t M, int64_t cus, bool bf) {
+double gemm_ks_cost(const Layout& L, int64_t M, int64_t cus, bool bf) {
     const bool wide = gemm_ks_wide(L, M, cus);
-    const int64_t bn = wide ? 256 : 128, tiles = ((M + kKsBM - 1) / kKsBM) * ((L.N + bn - 1) / bn);
-    return (tiles + cus - 1) / cus * gemm_ks_round_cost(L, wide, bf);
+    const double t = tiled_cost(wide ? kKs256 : kKs128, L, M, kKsBM, wide ? 256 : 128, 1, cus, bf, L.group % 128 == 0);
+    // With long K and at most 8 row tiles the 64 x 256 tiles run about an eighth
+    // faster than the fit has them (M = 512, K = 4096, N = 14336 66 us against
+    // 76): those rows of A stay in the L2 of every XCD.
+    return wide && M <= 512 && L.K >= 3072 ? 0.88 * t : t;
 }
 
 int launch_gemm_ks(const Layout& L, const uint16_t* A, const void* packed, uint16_t* C, int64_t M,

@@ -581,15 +581,28 @@ int launch_skinny_gemm(const Layout& L, const uint16_t* A, const void* packed, u
 int64_t gemm_workspace_bytes(const Layout& L, int64_t M);
 bool gemm256_supported(const Layout& L);
 int64_t gemm256_workspace_bytes(const Layout& L, int64_t M);
-// Expected time in nanoseconds with ws_bytes of workspace on cus compute units.
-int64_t gemm256_cost(const Layout& L, int64_t M, int64_t ws_bytes, int64_t cus, bool bf);
+// Expected times in microseconds on cus compute units.  tiled_cost: a kernel
+// with one workgroup per compute unit and tiles of bm x bn, K in S slices.
+struct TileCost {
+    double start;         // launch to first data
+    double round;         // fixed part of a round of workgroups
+    double small_group;   // factor of per_k for groups that are not whole 128-row chunks
+    double load_tbs;      // TB/s at which the XCDs fill their L2 together
+    double idle;          // part of per_k that an idle chip takes off
+    double once_tbs;      // TB/s of reading the operands and writing C once
+    double per_k[4];      // ns per row of K: W4 fp16, W4 bf16, W8 fp16, W8 bf16
+};
+double tiled_cost(const TileCost& c, const Layout& L, int64_t M, int64_t bm, int64_t bn, int64_t S, int64_t cus,
+                  bool bf, bool whole_groups);
+// With ws_bytes of workspace.
+double gemm256_cost(const Layout& L, int64_t M, int64_t ws_bytes, int64_t cus, bool bf);
 int launch_gemm256(const Layout& L, const uint16_t* A, const uint8_t* pk, uint16_t* C, int64_t M,
                    void* ws, size_t ws_bytes, hipStream_t s, bool bf);
 // The 64 x 128 GEMM with K split over the workgroup's waves (no workspace),
-// and its expected time in nanoseconds (of one round: a tile of BN columns).
+// its expected time, and that of one full round of 64 x 128 tiles.
 bool gemm_ks_supported(const Layout& L);
-int64_t gemm_ks_round_cost(const Layout& L, bool wide, bool bf);
-int64_t gemm_ks_cost(const Layout& L, int64_t M, int64_t cus, bool bf);
+double gemm_ks_round_cost(const Layout& L, bool bf);
+double gemm_ks_cost(const Layout& L, int64_t M, int64_t cus, bool bf);
 int launch_gemm_ks(const Layout& L, const uint16_t* A, const void* packed, uint16_t* C, int64_t M,
                    hipStream_t s, bool bf);
 // The same kernel over a range of the 256-row GEMM's 256 x 256 tiles: count
@@ -605,6 +618,9 @@ int launch_gemm_ks_range(const Layout& L, const uint16_t* A, const void* packed,
 // group.
 int launch_gemm_kq(const Layout& L, const uint16_t* A, const void* packed, uint16_t* C, int64_t M, int rb, int S,
                    void* ws, hipStream_t s, bool bf);
+// The 128 x 128 GEMM without a pipeline, for short K; any K and group.
+int launch_gemm_any(const Layout& L, const uint16_t* A, const void* packed, uint16_t* C, int64_t M,
+                    hipStream_t s, bool bf);
 int launch_gemm(const Layout& L, const uint16_t* A, const void* packed, uint16_t* C, int64_t M,
                 void* ws, size_t ws_bytes, hipStream_t s, bool bf);
 int launch_silu_mul(const uint16_t* gu, int64_t M, int64_t N, uint16_t* h, hipStream_t s, bool bf);

@@ -64,3 +64,33 @@ def test_one_round_streaming():
     for (bits, M, K, N, G, one), line in zip(want, got):
         assert line.startswith(f"gemv_kernel<{bits},{16 if M <= 16 else 32},8,"), line
         assert ("one-round" in line) == one, line
+
+
+def _kernel(line):
+    return line.split(" M=")[0].split(" rows=")[0]
+
+
+def test_short_k():
+    """Calls whose few steps a pipelined kernel cannot fill run the 128 x 128
+    kernel without one (both types: the second of each pair is bf16)."""
+    _skip_with_gpu()
+    from test_gpu_short_k import ANY_SHAPES
+    calls = [("gemm", b, bf, M, K, N, G, ws) for b, M, K, N, G in ANY_SHAPES + [(8, 2322, 576, 15560, 64), (4, 2547, 864, 14776, 96)]
+             for bf in (False, True) for ws in (True, False)]
+    for c, line in zip(calls, plans(calls)):
+        assert _kernel(line) == f"gemm_any_kernel<{c[1]},{'bf16' if c[2] else 'f16'}>", line
+
+
+def test_tiled_choice():
+    """The expected times know the width, the type, what the tiles load and how
+    much of the chip works: each of these calls once took a kernel that was 6 to
+    39% slower (measured) than the one named."""
+    _skip_with_gpu()
+    want = [((4, False, 2176, 9984, 944, 128), "gemm_kq_kernel<4,f16,8,8,"),     # 67 us, 64 x 64 tiles 99
+            ((8, True, 964, 14336, 4096, 64), "gemm256_kernel<8,2,bf16>"),        # 113, 128 x 128 tiles 124
+            ((8, True, 200, 32768, 8192, 128), "gemm_ks_kernel<8,1,bf16,128>"),   # 176, 64 x 64 tiles 187
+            ((8, False, 200, 32768, 8192, 128), "gemm_ks_kernel<8,1,f16,128>"),   # 149, 64 x 64 tiles 180
+            ((4, False, 512, 8320, 4096, 128), "gemm_ks_kernel<4,1,f16,128>"),    # 38, 128 x 128 tiles 42
+            ((4, False, 512, 8192, 4096, 128), "gemm_ks_kernel<4,1,f16,128>")]    # no step between the two
+    for (c, name), line in zip(want, plans([("gemm", *c, True) for c, _ in want])):
+        assert line.startswith(name), line
