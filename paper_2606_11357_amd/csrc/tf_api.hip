@@ -101,7 +101,8 @@ int gemm_entry(int bits, const uint16_t* A, const void* packed, uint16_t* C, int
     if (rc) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (M < tf::kSkinnyMinM) return tf::launch_gemv(L, A, packed, C, M, ws, s, bf);
-    if (M <= tf::kStreamMaxM) return tf::launch_skinny_gemm(L, A, packed, C, M, ws, s, bf);
+    if (M <= tf::kStreamMaxM || tf::stream64_size(L, M))
+        return tf::launch_skinny_gemm(L, A, packed, C, M, ws, s, bf);
     return tf::launch_gemm(L, A, packed, C, M, ws, ws_bytes, s, bf);
 }
 

@@ -3,7 +3,8 @@
 //
 // y[m, n] = sum_k x[m, k] * s[g, n] * (q[k, n] - z[g, n]),  1 <= M <= 8, on
 // the vector ALU only.  The same streaming kernel with 16 or 32 row slots
-// serves the GEMM entry points for few rows (skinny prefill, 4 <= M <= 32) on
+// serves the GEMM entry points for few rows (skinny prefill, 4 <= M <= 32; with
+// 64 slots 8-bit weights of short K, see stream64_size) on
 // the matrix cores (v_mfma_f32_16x16x32_f16 / _bf16), where the weights, not
 // the matrix cores, bound the time.  There the codes themselves (exact 16-bit
 // integers o + q) are the B operand: per group the matrix core forms
@@ -58,11 +59,14 @@ struct GemvCfg {
     static constexpr int T = BITS == 4 ? 4 : 2;      // columns per lane
     static constexpr int PW = BITS == 4 ? 64 : 32;   // panel width
     static constexpr bool FACT = M <= kFactMaxM;
-    // 16 or 32 row slots (GEMM calls with few rows): matrix cores, A read per
+    // 16, 32 or 64 row slots (GEMM calls with few rows): matrix cores, A read per
     // atom, MB blocks of 16 rows; the codes themselves are the B operand and
     // the scale and zero-point are applied per group
     static constexpr bool MF = M > TF_GEMV_MAX_M;
     static constexpr int MB = MF ? M / 16 : 1;
+    // 64 slots (8-bit weights, short K): the group sums would not fit in
+    // registers, so each weight is dequantized for the matrix core
+    static constexpr bool MFF = MF && M <= 32;
     static constexpr int XR = MF ? 1 : M;             // rows of x staged in LDS
     static constexpr int CR = FACT ? M : 1;           // rows of slice sums
 };
@@ -94,9 +98,9 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
     // (in bounds) and are never stored.
     using Cfg = GemvCfg<BITS, M>;
     constexpr int U = kGemvU, T = Cfg::T, PW = Cfg::PW;
-    constexpr bool FACT = Cfg::FACT, MF = Cfg::MF;
+    constexpr bool FACT = Cfg::FACT, MF = Cfg::MF, MFF = Cfg::MFF;
     constexpr int NT = WAVES * 64;
-    static_assert(!MF || M == 16 || M == 32, "the matrix-core form holds 16 or 32 rows");
+    static_assert(!MF || M == 16 || M == 32 || M == 64, "the matrix-core form holds 16, 32 or 64 rows");
     constexpr int MB = Cfg::MB;
     static_assert(SEG == 0 || U % SEG == 0, "segments tile a round");
     static_assert(U % D == 0, "the load ring tiles a round");
@@ -111,7 +115,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
     // (84 KB together at most, W4 with 3 rows; one workgroup per compute unit
     // either way), so a wave that has finished writes its sums while others
     // still read their staging, with no barrier in between; the matrix-core
-    // form's reduction buffer (up to 32 rows) reuses the staging storage.
+    // form's reduction buffer (up to 64 rows) reuses the staging storage.
     struct SmemApart {
         Stage st[WAVES];
         float red[WAVES][M][PW];
@@ -267,9 +271,9 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
         DqConst<BF> kq[TE];              // dequant form: the open segment's scale and zero-point
         // matrix-core form: the open segment's sums of A x code and
         // of A (row sums, the same in every column of a block)
-        float4_t accg[MF ? MB : 1][MF ? T : 1], rsum[MF ? MB : 1];
+        float4_t accg[MFF ? MB : 1][MFF ? T : 1], rsum[MFF ? MB : 1];
         auto open = [&]() {
-            if constexpr (MF) {
+            if constexpr (MFF) {
 #pragma unroll
                 for (int b = 0; b < MB; ++b) {
                     rsum[b] = float4_t{0.f, 0.f, 0.f, 0.f};
@@ -295,7 +299,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
         // form: y += s * (acc - (o + z) * (row sum of A)), o the
         // codes' offset
         auto close = [&]() {
-            if constexpr (MF) {
+            if constexpr (MFF) {
                 const uint16_t* sp = reinterpret_cast<const uint16_t*>(sbytes + (gl * PW + c * T) * 2);
                 const uint8_t* zp = zbytes + gl * PW + c * T;
                 constexpr float off = BF ? (BITS == 4 ? 128.f : 0.f) : 1024.f;
@@ -323,7 +327,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
             }
         };
 
-        if constexpr (FACT || MF || SEG > 0) open();
+        if constexpr (FACT || MFF || SEG > 0) open();
 #pragma unroll
         for (int i = 0; i < U; ++i) {
             const int j = r * U + i;      // atom of the run
@@ -339,7 +343,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
                     if constexpr (!ONE) aring[b][i % D] = load_afrag(b, j + D);
                 }
             }
-            if constexpr (MF) {
+            if constexpr (MFF) {
                 // row sums of this atom's A, by the matrix core against ones
                 const uint32_t one2 = BF ? 0x3F803F80u : 0x3C003C00u;
                 const u32x4 ones = {one2, one2, one2, one2};
@@ -347,7 +351,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
                 for (int b = 0; b < MB; ++b) rsum[b] = mfma16<BF>(afrag[b], ones, rsum[b]);
             }
             // dequant form, group size known at run time: this atom's metadata
-            if constexpr (!FACT && !MF && SEG == 0) open();
+            if constexpr (!FACT && !MFF && SEG == 0) open();
             u32x4 xv[Cfg::XR];
             if constexpr (!MF) {
 #pragma unroll
@@ -374,7 +378,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
 #pragma unroll
             for (int t = 0; t < TE; ++t) {
                 uint32_t P[4];
-                if constexpr (MF) {
+                if constexpr (MFF) {
                     // the codes as exact 16-bit integers o + q: fp16 1024 + q,
                     // bf16 128 + q (4-bit) or q (8-bit, converted)
                     if constexpr (BITS == 4) {
@@ -416,6 +420,12 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
                 } else {
                     const u32x4 wu = dq_operand<BF, BITS>(wd[BITS == 4 ? t : 2 * t], wd[BITS == 4 ? t : 2 * t + 1],
                                                           magic, kq[t]);
+                    if constexpr (MF) {
+                        // the dequantized dword is the B operand of columns c + 16 t
+#pragma unroll
+                        for (int b = 0; b < MB; ++b) macc[b][t] = mfma16<BF>(afrag[b], wu, macc[b][t]);
+                        continue;
+                    }
 #pragma unroll
                     for (int q = 0; q < 4; ++q) P[q] = wu[q];
                 }
@@ -443,7 +453,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemv_kernel(
                         ++gl;
                         pos = 0;
                     }
-                    if constexpr (FACT || MF || SEG > 0) open();
+                    if constexpr (FACT || MFF || SEG > 0) open();
                 }
             }
         }
@@ -687,9 +697,10 @@ int launch_g(const Layout& L, const uint16_t* A, const uint8_t* pk, uint16_t* C,
     // asking for everything first only delays the first atom: 3% (16 slots) and 8%
     // (32) slower at every N, so those keep the ring; 4-bit groups of 64 and 96 and 8-bit groups
     // of 32 lose 1-8% on few workgroups and gain 0-20% from 128 on.
-    const bool one_round = RW == kGemvU && (L.group >= (BITS == 8 ? 64 : 128) ||
+    const bool one_round = M <= 32 && RW == kGemvU && (L.group >= (BITS == 8 ? 64 : 128) ||
                                             (L.np * S >= 128 && L.group >= (BITS == 8 ? 32 : 64)));
-    if (one_round) return go(gemv_kernel<BITS, M, WAVES, SEG, kGemvU, BF, 1>, kGemvU, 1);
+    if constexpr (M <= 32)
+        if (one_round) return go(gemv_kernel<BITS, M, WAVES, SEG, kGemvU, BF, 1>, kGemvU, 1);
     return go(gemv_kernel<BITS, M, WAVES, SEG, gemv_ring_for(M), BF, 1>, gemv_ring_for(M), 1);
 }
 
@@ -730,8 +741,8 @@ int64_t gemv_workspace_bytes(const Layout& L, int64_t M) {
     return M >= 1 && M <= TF_GEMV_MAX_M ? workspace_for_slots(L, M) : 0;
 }
 
-// row slots of the matrix-core form for M rows: 16 or 32 (64: only the
-// promised workspace of 33..64 rows, see tf_internal.h)
+// row slots of the matrix-core form for M rows (33..64 rows with 4-bit
+// weights: only the promised workspace, see tf_internal.h)
 static int64_t skinny_slots(int64_t M) { return M <= 16 ? 16 : M <= 32 ? 32 : 64; }
 
 int64_t skinny_workspace_bytes(const Layout& L, int64_t M) {
@@ -753,14 +764,35 @@ int launch_skinny_bits(const Layout& L, const uint16_t* A, const uint8_t* pk, ui
                        int64_t M, void* ws, hipStream_t s) {
     switch (skinny_slots(M)) {
         case 16: return launch_m<BITS, 16, BF>(L, A, pk, C, ws, s, (int)M);
-        default: return launch_m<BITS, 32, BF>(L, A, pk, C, ws, s, (int)M);
+        case 32: return launch_m<BITS, 32, BF>(L, A, pk, C, ws, s, (int)M);
+        default:
+            if constexpr (BITS == 8) return launch_m<BITS, 64, BF>(L, A, pk, C, ws, s, (int)M);
+            return TF_ERR_ARG;
     }
 }
 }  // namespace
 
+// 33 to 64 rows: 64 row slots for 8-bit weights while K is short and one round
+// of workgroups covers the panels.  The streaming form then ends before the
+// tiled kernel has filled its rings and added its eight parts of K; its time
+// grows faster with K, steps up at the fourth row block, and is longer where
+// the rows of A start on cache lines (they compete for the same sets of the
+// L1).  Measured on MI355X against 64 x 64 tiles (us, means of 3800 shapes), up
+// to 48 rows: rows off the lines K = 640 5.8 against 6.9, 1280 7.8, 8.1, 2048
+// 11.0, 10.4; on the lines, whole groups K = 512 5.6, 5.9, 768 6.7, 6.7, other
+// groups K = 640 6.4, 6.8, 1280 9.1, 8.2; more rows: off the lines K = 640 6.1,
+// 6.9, 1280 8.7, 8.1, on the lines K = 384 5.4, 5.7, 512 6.2, 5.9.  With 4-bit
+// weights the tiles win or tie within 2% on average.
+bool stream64_size(const Layout& L, int64_t M) {
+    if (L.bits != 8 || M <= kStreamMaxM || M > kSkinnyMaxM || L.np > kTargetWorkgroups) return false;
+    const bool few = M <= 48, whole_groups = L.na % 4 == 0 && L.group % 128 == 0;
+    if (L.na % 2 != 0) return L.K <= (few ? 1888 : 1056);
+    return L.K <= (!few ? 384 : whole_groups ? 640 : 1024);
+}
+
 int launch_skinny_gemm(const Layout& L, const uint16_t* A, const void* packed, uint16_t* C,
                        int64_t M, void* ws, hipStream_t s, bool bf) {
-    if (M < 1 || M > kStreamMaxM) return TF_ERR_ARG;
+    if (M < 1 || !(M <= kStreamMaxM || stream64_size(L, M))) return TF_ERR_ARG;
     const uint8_t* pk = static_cast<const uint8_t*>(packed);
     if (bf)
         return L.bits == 4 ? launch_skinny_bits<4, true>(L, A, pk, C, M, ws, s)

@@ -54,7 +54,7 @@ constexpr int kSkMaxGroups = 256;
 // the tiled GEMMs (from 33 rows the streaming kernel, every weight dequantized
 // for 64 row slots, is slower than one round of 64 x 64 tiles: K = 4096,
 // N = 14336, M = 33, 64 W4 17.4, 25.4 against 13.6, 14.8 us, W8 M = 64 46
-// against 17 us).  The workspace promised up to kSkinnyMaxM rows is the
+// against 17 us; but for 8-bit weights of short K, see stream64_size).  The workspace promised up to kSkinnyMaxM rows is the
 // streaming kernel's.
 constexpr int kSkinnyMinM = 4;
 constexpr int kStreamMaxM = 32;
@@ -576,6 +576,7 @@ int64_t gemv_workspace_bytes(const Layout& L, int64_t M);
 int64_t skinny_workspace_bytes(const Layout& L, int64_t M);
 int launch_gemv(const Layout& L, const uint16_t* A, const void* packed, uint16_t* C, int64_t M,
                 void* ws, hipStream_t s, bool bf);
+bool stream64_size(const Layout& L, int64_t M);    // 33..64 rows that stay on it
 int launch_skinny_gemm(const Layout& L, const uint16_t* A, const void* packed, uint16_t* C,
                        int64_t M, void* ws, hipStream_t s, bool bf);
 int64_t gemm_workspace_bytes(const Layout& L, int64_t M);

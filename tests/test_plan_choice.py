@@ -81,6 +81,22 @@ def test_short_k():
         assert _kernel(line) == f"gemm_any_kernel<{c[1]},{'bf16' if c[2] else 'f16'}>", line
 
 
+def test_short_k_few_rows():
+    """33 to 64 rows of 8-bit weights stay on the streaming kernel where it ends
+    before the tiled one has started: short K, sooner with more than 48 rows and
+    where the rows of A start on cache lines, and only in one round of panels."""
+    _skip_with_gpu()
+    from test_gpu_short_k import STREAM64_SHAPES
+    want = [(c, True) for c in STREAM64_SHAPES + [(8, 48, 1888, 600, 32), (8, 64, 1056, 600, 32), (8, 48, 1024, 600, 64)]]
+    want += [(c, False) for c in [(8, 48, 1920, 600, 32), (8, 64, 1120, 600, 32), (8, 48, 768, 600, 128),
+                                  (8, 64, 448, 600, 64), (8, 48, 480, 8200, 32), (8, 65, 480, 600, 32),
+                                  (4, 48, 480, 600, 32)]]
+    calls = [("gemm", b, bf, M, K, N, G, ws) for (b, M, K, N, G), _ in want for bf in (False, True) for ws in (True, False)]
+    stays = [stay for _, stay in want for _ in range(4)]
+    for c, stay, line in zip(calls, stays, plans(calls)):
+        assert line.startswith("gemv_kernel<8,64," if stay else ("gemm_kq_kernel<", "gemm_any_kernel<")), line
+
+
 def test_tiled_choice():
     """The expected times know the width, the type, what the tiles load and how
     much of the chip works: each of these calls once took a kernel that was 6 to
