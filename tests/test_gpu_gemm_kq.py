@@ -25,6 +25,7 @@ pytestmark = pytest.mark.gpu
 SHAPES = [
     (4, 33, 32, 8, 32),           # one step: seven of the eight waves idle
     (8, 64, 96, 72, 96),          # three steps, a group that is no power of two
+    (8, 65, 96, 72, 96),          # ... on the tiles (64 rows of 8-bit weights with short K stream)
     (4, 65, 160, 136, 32),        # a group a step, two row tiles, ragged columns
     (8, 129, 1376, 264, 32),      # 43 steps: a last half pair, and runs of 4 and 6 steps
     (4, 200, 1344, 520, 192),     # groups of six steps against pairs
@@ -35,7 +36,7 @@ SHAPES = [
     (4, 49, 4096, 1032, 128),     # whole chunks, 64 x 64 tiles, K in two slices
     (8, 64, 14336, 264, 256),     # ... and more, groups of two chunks
     (4, 200, 14336, 1032, 128),   # 128-row promise of workspace, K split
-    (4, 520, 14336, 2056, 128),   # 128 x 128 tiles, K split
+    (4, 520, 14336, 2056, 128),   # 128 x 128 tiles, K split (with a workspace)
 ]
 
 

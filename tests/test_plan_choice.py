@@ -110,3 +110,27 @@ def test_tiled_choice():
             ((4, False, 512, 8192, 4096, 128), "gemm_ks_kernel<4,1,f16,128>")]    # no step between the two
     for (c, name), line in zip(want, plans([("gemm", *c, True) for c, _ in want])):
         assert line.startswith(name), line
+
+
+def test_kernels_of_the_gpu_tests():
+    """The shapes of the GPU tests that are named for a kernel run that kernel:
+    the GEMMs of middle sizes, and each form of the 256-row GEMM for every width
+    and number of groups in a chunk."""
+    _skip_with_gpu()
+    import test_gpu_gemm256 as big
+    import test_gpu_gemm_kq as kq
+    # 64 rows of 8-bit weights with three steps now stream; long K without a
+    # workspace takes the tiles that need none
+    calls = [("gemm", b, bf, M, K, N, G, ws) for b, M, K, N, G in kq.SHAPES for bf in (False, True) for ws in (True, False)
+             if (b, M, K) != (8, 64, 96) and (ws or M != 520)]
+    for c, line in zip(calls, plans(calls)):
+        assert line.startswith(f"gemm_kq_kernel<{c[1]},"), line
+    calls = [("gemm", b, bf, M, K, N, G, True) for b, M, K, N, G, _ in big.SHAPES for bf in (False, True)]
+    forms = [form for *_, form in big.SHAPES for _ in range(2)]
+    seen = set()
+    for c, form, line in zip(calls, forms, plans(calls)):
+        groups = 128 // min(c[6], 128)
+        assert line.startswith(f"gemm256_kernel<{c[1]},{groups},{'bf16' if c[2] else 'f16'}>"), line
+        assert form in line, line
+        seen.add((c[1], groups, form))
+    assert {(b, g, f) for b in (4, 8) for g in (1, 2, 4) for f in (", stream-K,", "whole tiles")} <= seen
