@@ -17,11 +17,15 @@ from test_gpu_parity import dev, pack, tf  # noqa: F401
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-CASES = [("gemm", 4, 1100, 1024, 2320),   # 256-row tiles, stream-K
-         ("gemm", 4, 200, 12288, 520),    # 128-row tiles, split-K
-         ("gemm", 4, 200, 1024, 520),     # 64 x 128 tiles, K over the waves
-         ("gemm", 4, 512, 512, 14336),    # 64 x 256 tiles, K over the waves
-         ("gemm", 4, 40, 4096, 1024),     # streaming matrix-core form, 64 row slots
+CASES = [("gemm", 4, 1100, 1024, 2320),   # 128 x 128 tiles (stream-K under replay: test_gpu_gemm256.py)
+         ("gemm", 4, 200, 12288, 520),    # 64 x 64 tiles, K split
+         ("gemm", 4, 200, 1024, 520),     # 64 x 64 tiles, K over the waves
+         ("gemm", 4, 512, 512, 14336),    # 256-row tiles, whole
+         ("gemm", 4, 257, 2176, 11000),   # 64 x 256 tiles, K over the waves
+         ("gemm", 8, 129, 640, 6152),     # 64 x 128 tiles, K over the waves
+         ("gemm", 4, 900, 128, 2056),     # 128 x 128 tiles without a pipeline
+         ("gemm", 8, 48, 384, 520),       # streaming matrix-core form, 64 row slots
+         ("gemm", 4, 40, 4096, 1024),     # 64 x 64 tiles
          ("gemm", 4, 20, 14336, 4096),    # streaming matrix-core form, factored, K split
          ("gemv", 4, 1, 14336, 4096),     # decode GEMV, K split
          ("gemv", 4, 1, 4096, 4096),      # decode GEMV, 4 column parts per panel

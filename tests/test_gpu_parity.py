@@ -184,7 +184,7 @@ GEMM_SHAPES = [(4, 16, 2048, 2048, 128), (4, 17, 256, 136, 128), (4, 129, 512, 2
                # 17..64 rows: two or four row blocks of the streaming form
                (4, 24, 1024, 520, 128), (8, 31, 512, 72, 64), (4, 48, 2048, 264, 32), (8, 64, 1024, 2056, 128),
                (4, 40, 768, 136, 256),
-               # 256..1023 rows with K >= 8192: the 256-row kernel (stream-K), partial row tiles
+               # 256..1023 rows with K >= 8192: K slices, partial row tiles
                (4, 300, 8192, 520, 128), (8, 600, 8192, 264, 64), (4, 257, 16384, 136, 32),
                # the 64 x 128 kernel with K split over the workgroup's waves: 8-bit with
                # 192..256 tiles (ragged N with a clamped last panel; 9 and 5 chunks split
@@ -193,8 +193,7 @@ GEMM_SHAPES = [(4, 16, 2048, 2048, 128), (4, 17, 256, 136, 128), (4, 129, 512, 2
                # ... with 4-bit tiles of 64 x 256 (more than 1.5 rounds of 64 x 128 tiles): ragged
                # rows, columns (the last tile partly past N) and K (31 chunks), groups of 32 and 64
                (4, 1000, 3968, 4088, 32), (4, 300, 4096, 11008, 64), (4, 256, 4096, 14336, 128),
-               # the 128-row GEMM: 4-bit beyond the 64 x 128 kernel's 1200 tiles, and
-               # long K on few tiles (split-K)
+               # 4-bit with more than 1200 tiles of 64 x 128, and long K on few tiles (K slices)
                (4, 1000, 1024, 10000, 128), (4, 200, 12288, 520, 128), (8, 100, 16384, 264, 64),
                # 260 tiles of 256 x 256: one whole-tile round, the last 4 tiles (a partial
                # row tile, ragged N) by the 64 x 128 kernel, some of its parts wholly past C
@@ -293,7 +292,7 @@ def test_workspace_shared_across_shapes(tf):
                                            (4, 12, 16384, 512, 128), (8, 16, 14336, 1024, 128),
                                            (4, 1300, 2048, 1000, 128), (8, 1520, 1024, 776, 64),
                                            (4, 2048, 1024, 4096, 32), (4, 1100, 3072, 2320, 128),
-                                           # 128-row tiles split along K (few tiles, long K)
+                                           # K slices (few tiles, long K)
                                            (4, 200, 12288, 1024, 128), (8, 100, 16384, 520, 64),
                                            (8, 40, 8192, 264, 32), (4, 64, 8192, 1024, 128),
                                            (8, 40, 4096, 4096, 128), (8, 256, 4096, 4096, 128),
@@ -302,9 +301,8 @@ def test_workspace_shared_across_shapes(tf):
                                            (4, 300, 2048, 520, 64), (4, 700, 1536, 1000, 128),
                                            (4, 100, 4096, 9400, 128)])
 def test_gemm_workspace_modes(tf, bits, M, K, N, G):
-    """The K-split kernels (workspace: stream-K for 256-row tiles, split-K for
-    128-row tiles) and the whole-tile kernels (no workspace) both meet the
-    bar; a split result is bitwise repeatable and its workspace serves the
+    """The kernels that a workspace lets split K and those that run without one
+    both meet the bar (the 256-row GEMM's stream-K: test_gpu_gemm256.py); a split result is bitwise repeatable and its workspace serves the
     next call at once."""
     d = make_inputs(bits, M, K, N, group=G, seed=M + N)
     packed = pack(tf, d)
@@ -320,7 +318,7 @@ def test_gemm_workspace_modes(tf, bits, M, K, N, G):
 
 
 def test_workspace_shared_gemm_gemv(tf):
-    """One workspace serves split-K GEMVs and stream-K GEMMs in turn."""
+    """One workspace serves split-K GEMVs and GEMMs in turn (stream-K: test_gpu_gemm256.py)."""
     cases = [("gemm", 4, 1300, 1024, 1000), ("gemv", 4, 1, 14336, 4096), ("gemm", 8, 1600, 2048, 520),
              ("gemv", 8, 3, 8192, 520), ("gemm", 4, 1300, 1024, 1000), ("gemm", 8, 300, 4096, 1024),
              ("gemm", 4, 12, 8192, 512), ("gemm", 4, 200, 2048, 2000)]

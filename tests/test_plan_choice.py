@@ -114,17 +114,22 @@ def test_tiled_choice():
 
 def test_kernels_of_the_gpu_tests():
     """The shapes of the GPU tests that are named for a kernel run that kernel:
-    the GEMMs of middle sizes, and each form of the 256-row GEMM for every width
-    and number of groups in a chunk."""
+    the GEMMs of middle sizes, the K-split GEMM's tiles, and each form of the
+    256-row GEMM for every width and number of groups in a chunk."""
     _skip_with_gpu()
     import test_gpu_gemm256 as big
     import test_gpu_gemm_kq as kq
+    import test_gpu_gemm_ks as ks
     # 64 rows of 8-bit weights with three steps now stream; long K without a
     # workspace takes the tiles that need none
     calls = [("gemm", b, bf, M, K, N, G, ws) for b, M, K, N, G in kq.SHAPES for bf in (False, True) for ws in (True, False)
              if (b, M, K) != (8, 64, 96) and (ws or M != 520)]
     for c, line in zip(calls, plans(calls)):
         assert line.startswith(f"gemm_kq_kernel<{c[1]},"), line
+    calls = [("gemm", b, bf, M, K, N, G, ws) for b, M, K, N, G, _ in ks.SHAPES for bf in (False, True) for ws in (True, False)]
+    tiles = [t for *_, t in ks.SHAPES for _ in range(4)]
+    for c, t, line in zip(calls, tiles, plans(calls)):
+        assert line.startswith(f"gemm_ks_kernel<{c[1]},{128 // c[6]},") and t in line, line
     calls = [("gemm", b, bf, M, K, N, G, True) for b, M, K, N, G, _ in big.SHAPES for bf in (False, True)]
     forms = [form for *_, form in big.SHAPES for _ in range(2)]
     seen = set()
