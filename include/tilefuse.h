@@ -155,11 +155,12 @@ int64_t tf_gemm_workspace_bytes(int bits, int64_t M, int64_t K, int64_t N, int g
  *   C_f16[M, N] = A_f16[M, K] x dequant(packed)[K, N], fp32 accumulate, RNE.
  * Any M >= 1.  M <= 3 runs the decode GEMV; 4 <= M <= 32 a weight-streaming
  * kernel on the matrix cores (16 or 32 row slots); larger M the tiled
- * matrix-core GEMMs.  The tiled GEMMs feed the matrix cores the dequantized
- * fp16 weight RNE(s * (q - z)), rounded once; the streaming kernel feeds the
- * codes themselves and applies scale and zero-point to each group's sums
- * (Eq. 2 summed over a group), so no weight is rounded (as in the decode GEMV
- * up to 4 rows).
+ * matrix-core GEMMs, or, up to 64 rows of 8-bit weights with short K, the
+ * streaming kernel with 64 row slots.  The tiled GEMMs and the 64-slot form
+ * feed the matrix cores the dequantized fp16 weight RNE(s * (q - z)), rounded
+ * once; up to 32 rows the streaming kernel feeds the codes themselves and
+ * applies scale and zero-point to each group's sums (Eq. 2 summed over a
+ * group), so no weight is rounded (as in the decode GEMV up to 4 rows).
  * workspace: see tf_workspace_bytes.
  */
 int tf_w4a16_gemm(const uint16_t* A_f16, const void* packed, uint16_t* C_f16,

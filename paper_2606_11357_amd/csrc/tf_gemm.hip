@@ -36,8 +36,8 @@ int64_t tiles_of(const Layout& L, int64_t M, int64_t bm, int64_t bn) {
 // groups of 32 to 256, both widths and types.  Where a kernel is within 35%
 // of the best one its expected time is within 5 to 9% in nine of ten cases
 // and 25% in all; the kernel chosen is 0.1% (geometric mean) slower than the best
-// one, at most 14%.  (Without width, type and loads, as rounds of a fixed time:
-// 1.7%, at most 63%.)
+// one, at most 19%.  (As rounds of a fixed time, without width, type, loads and
+// the kernel for short K: 1.7%, at most 96%.)
 double tiled_cost(const TileCost& c, const Layout& L, int64_t M, int64_t bm, int64_t bn, int64_t S, int64_t cus,
                   bool bf, bool whole_groups) {
     const int64_t tm = (M + bm - 1) / bm, tn = (L.N + bn - 1) / bn, units = tm * tn * S;

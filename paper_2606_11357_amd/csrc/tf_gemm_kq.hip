@@ -30,10 +30,10 @@
 // M = 256: 2.4 us to the first data, 0.75 us a step of 64 MFMAs (0.45 at the
 // matrix core's rate; a copy without loads 0.7, without MFMAs 0.54: one wave
 // issues everything, at about 5 cycles an instruction), 4.2 us to add and store
-// the quarters.  64 x 64, M = 64: one wave per SIMD took 0.36 us a step, two
+// the parts.  64 x 64, M = 64: one wave per SIMD took 0.36 us a step, two
 // take 0.25 each pair (12.0 -> 7.9 us the loop), since one wave's matrix
 // instructions then run under the other's vector work.
-// Measured against what served these calls before (graph replay, fp16, us):
+// Measured against what served these calls otherwise (graph replay, fp16, us):
 // 333 x 1376 x 2048 groups of 32 (a 128 x 128 kernel for any group, single
 // buffered) 33.9 -> 8.6; 64 x 4096 x 14336 (streaming form) 25.4 -> 12.8, W8
 // 46 -> 17; 200 x 14336 x 4096 (128 x 256 tiles, split K) 47.8 -> 33.2;
@@ -56,7 +56,7 @@ struct KqCfg {
     static constexpr int WAVES = RB == 8 ? 4 : 8;
     static constexpr int RING = 2;                         // A buffers (pairs of steps) per wave
     static constexpr int PAIR_BYTES = 16 * RB * 128;
-    static constexpr int SUMB = NB < 2 * RING ? NB : 2 * RING;   // column blocks per pass of the quarters' sum
+    static constexpr int SUMB = NB < 2 * RING ? NB : 2 * RING;   // column blocks per pass of the waves' sum
 };
 
 // The vector-memory operations a wave issues around step t (negative t: the
@@ -168,7 +168,7 @@ __global__ __launch_bounds__((64 * KqCfg<RB, NB>::WAVES), 1) void gemm_kq_kernel
     const int64_t row0 = (int64_t)tm * BM, col0 = (int64_t)tn * BN;
 
     // K ranges in blocks of KB steps (a chunk, or a pair): the slice's, then
-    // this wave's quarter of it; possibly empty.
+    // this wave's part of it; possibly empty.
     constexpr int KB = G4 ? 4 : 2;
     const int nblk = (na + KB - 1) / KB;
     const int sb0 = (int)((int64_t)slice * nblk / sk.S), sb1 = (int)((int64_t)(slice + 1) * nblk / sk.S);
@@ -450,9 +450,9 @@ __global__ __launch_bounds__((64 * KqCfg<RB, NB>::WAVES), 1) void gemm_kq_kernel
     }
     mfma_hazard_gap();
 
-    // Sum the four K quarters in quarter order, SUMB column blocks per pass:
-    // every wave parks its sums, then wave w adds a quarter of the blocks of
-    // all four.  The weights were the first MFMA operand: lane (c, kg) holds
+    // Sum the waves' parts of K in wave order, SUMB column blocks per pass:
+    // every wave parks its sums, then each adds its share of the blocks of
+    // all of them.  The weights were the first MFMA operand: lane (c, kg) holds
     // row c of a block and its columns 4 kg .. 4 kg + 3 (N % 8 == 0, so all
     // four or none fit).
     float4_t* const red = reinterpret_cast<float4_t*>(lds);
